@@ -72,6 +72,15 @@ const char *cd_version(void);
 size_t cd_workspace_bytes(int64_t B, int64_t N, int64_t M);
 
 /*
+ * Bytes of device workspace with which cd_forward takes its fastest path for
+ * this shape: cd_workspace_bytes, or more (about 50 bytes per point) where
+ * sorting the clouds and skipping far targets is faster than all pairs (from
+ * about 7e8 pairs on).  The results are the same bits either way.  0 where
+ * cd_workspace_bytes is.
+ */
+size_t cd_workspace_bytes_best(int64_t B, int64_t N, int64_t M);
+
+/*
  * Nearest neighbours in both directions (Sec. 2.5: the point matching that
  * the Chamfer distance is built on).
  *   X [B,N,3], Y [B,M,3]      input clouds (device, float32)
@@ -82,7 +91,8 @@ size_t cd_workspace_bytes(int64_t B, int64_t N, int64_t M);
  *                              cd_workspace_bytes(B,N,M) bytes, 256-byte
  *                              aligned; its contents on entry are ignored and
  *                              on exit are unspecified.  CD_ERR_WORKSPACE if
- *                              too small.
+ *                              too small.  With cd_workspace_bytes_best(B,N,M)
+ *                              bytes or more the fastest path is taken.
  * Results are bitwise reproducible from run to run.
  */
 cd_status cd_forward(int64_t B, int64_t N, int64_t M,

@@ -31,7 +31,7 @@ from typing import Optional, Tuple
 import torch
 
 __all__ = [
-    "CDError", "LIB_PATH", "library", "workspace_bytes", "nn_distance", "nn_distance_noalloc",
+    "CDError", "LIB_PATH", "library", "workspace_bytes", "workspace_bytes_best", "nn_distance", "nn_distance_noalloc",
     "FORWARD_NOALLOC_MAX_BYTES", "chamfer_reduce",
     "f_score", "metrics", "chamfer_backward", "chamfer_backward_pointwise", "chamfer_distance",
     "ChamferDistance", "forward_step", "mesh_sample_faces", "mesh_sample_points",
@@ -67,6 +67,8 @@ def library() -> ctypes.CDLL:
     lib.cd_version.argtypes = []
     lib.cd_workspace_bytes.restype = ctypes.c_size_t
     lib.cd_workspace_bytes.argtypes = [i64, i64, i64]
+    lib.cd_workspace_bytes_best.restype = ctypes.c_size_t
+    lib.cd_workspace_bytes_best.argtypes = [i64, i64, i64]
     lib.cd_forward.restype = st
     lib.cd_forward.argtypes = [i64, i64, i64, vp, vp, vp, vp, vp, vp, vp, ctypes.c_size_t, vp]
     lib.cd_reduce.restype = st
@@ -169,15 +171,18 @@ def _distances(dist_xy: torch.Tensor, dist_yx: torch.Tensor) -> Tuple[torch.Tens
     return dxy, dyx
 
 
-def _workspace(ws: Optional[torch.Tensor], need: int, device: torch.device) -> torch.Tensor:
+def _forward_workspace(ws: Optional[torch.Tensor], B: int, N: int, M: int,
+                       device: torch.device) -> torch.Tensor:
     """The caller's workspace if it is a large enough uint8 tensor on `device`,
-    else a new one."""
+    else a new one (of the size with which cd_forward is fastest)."""
+    lib = library()
     if ws is not None:
         ws = _device_tensor(ws, "workspace", torch.uint8)
         if ws.device != device:
             raise ValueError(f"workspace must be on {device} (got {ws.device})")
-        if ws.numel() >= need:
+        if ws.numel() >= int(lib.cd_workspace_bytes(B, N, M)):
             return ws
+    need = int(lib.cd_workspace_bytes_best(B, N, M))
     return torch.empty(max(need, 1), dtype=torch.uint8, device=device)
 
 
@@ -194,6 +199,11 @@ def workspace_bytes(B: int, N: int, M: int) -> int:
     return int(library().cd_workspace_bytes(B, N, M))
 
 
+def workspace_bytes_best(B: int, N: int, M: int) -> int:
+    """Device workspace (bytes) with which cd_forward is fastest for this shape."""
+    return int(library().cd_workspace_bytes_best(B, N, M))
+
+
 def nn_distance(X: torch.Tensor, Y: torch.Tensor, workspace: Optional[torch.Tensor] = None
                 ) -> Tuple[torch.Tensor, torch.Tensor, torch.Tensor, torch.Tensor]:
     """Nearest neighbours both ways: (dist_xy [B,N], idx_xy [B,N], dist_yx [B,M], idx_yx [B,M])."""
@@ -205,7 +215,7 @@ def nn_distance(X: torch.Tensor, Y: torch.Tensor, workspace: Optional[torch.Tens
     dist_yx = torch.empty((B, M), dtype=torch.float32, device=dev)
     idx_yx = torch.empty((B, M), dtype=torch.int32, device=dev)
     lib = library()
-    workspace = _workspace(workspace, int(lib.cd_workspace_bytes(B, N, M)), dev)
+    workspace = _forward_workspace(workspace, B, N, M, dev)
     with torch.cuda.device(dev):
         _check(lib.cd_forward(B, N, M, _ptr(X), _ptr(Y), _ptr(dist_xy), _ptr(idx_xy),
                               _ptr(dist_yx), _ptr(idx_yx), _ptr(workspace), workspace.numel(),

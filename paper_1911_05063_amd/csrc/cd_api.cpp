@@ -86,6 +86,14 @@ size_t cd_workspace_bytes(int64_t B, int64_t N, int64_t M)
     return cdk::forward_workspace_bytes(cdk::plan_forward(B, N, M));
 }
 
+size_t cd_workspace_bytes_best(int64_t B, int64_t N, int64_t M)
+{
+    const size_t need = cd_workspace_bytes(B, N, M);
+    if (need == 0) return 0;
+    const cdk::TreePlan tree = cdk::plan_tree(B, N, M);
+    return tree.use ? std::max(need, tree.bytes) : need;
+}
+
 cd_status cd_forward(int64_t B, int64_t N, int64_t M, const float *X, const float *Y,
                      float *dist_xy, int32_t *idx_xy, float *dist_yx, int32_t *idx_yx, void *ws,
                      size_t ws_bytes, hipStream_t stream)
@@ -104,7 +112,10 @@ cd_status cd_forward(int64_t B, int64_t N, int64_t M, const float *X, const floa
     if (!aligned256(ws)) return invalid("workspace not 256-byte aligned");
     if (cdk::forward_tiles(plan) > 2147483647LL) return invalid("too many tiles for one launch");
     const cdk::FwdArgs args{X, Y, dist_xy, idx_xy, dist_yx, idx_yx, ws};
-    const hipError_t e = cdk::launch_forward(plan, args, stream);
+    const cdk::TreePlan tree = cdk::plan_tree(B, N, M);
+    const hipError_t e = tree.use && ws_bytes >= tree.bytes
+                             ? cdk::launch_tree(tree, N, M, args, stream)
+                             : cdk::launch_forward(plan, args, stream);
     if (e != hipSuccess) return hip_failed(e, "cd_forward launch");
     return CD_OK;
 }
@@ -134,7 +145,9 @@ cd_status cd_forward_noalloc(int64_t B, int64_t N, int64_t M, const float *X, co
     hipError_t e = cdk::forward_scratch(stream, &ws);
     if (e != hipSuccess) return hip_failed(e, "cd_forward_noalloc scratch address");
     const cdk::FwdArgs args{X, Y, dist_xy, idx_xy, dist_yx, idx_yx, ws};
-    e = cdk::launch_forward(plan, args, stream);
+    const cdk::TreePlan tree = cdk::plan_tree(B, N, M);
+    e = tree.use && tree.bytes <= cdk::kForwardScratchBytes ? cdk::launch_tree(tree, N, M, args, stream)
+                                                            : cdk::launch_forward(plan, args, stream);
     if (e != hipSuccess) return hip_failed(e, "cd_forward_noalloc launch");
     return CD_OK;
 }

@@ -41,6 +41,18 @@ int64_t forward_tiles(const FwdPlan &plan);
 
 hipError_t launch_forward(const FwdPlan &plan, const FwdArgs &args, hipStream_t stream);
 
+// Pruned search (nn_tree.hip): the same results from sorted clouds.
+struct TreePlan {
+    bool use;            // the shape gains from it
+    int64_t B;
+    bool bucket;         // some cloud has several ranges
+    int32_t ranges[2], log_c[2], chunks[2], nodes[2];
+    size_t entries[2], offs[2], curve[2], rec[2], leaf[2], node[2], list, bytes;   // workspace offsets and size
+};
+TreePlan plan_tree(int64_t B, int64_t N, int64_t M);
+hipError_t launch_tree(const TreePlan &plan, int64_t N, int64_t M, const FwdArgs &args,
+                       hipStream_t stream);
+
 // The no-allocation forward's workspace: a static device array of this many
 // bytes per GPU.  forward_scratch() gives its address on the device of
 // `stream` (looked up once per device, with that device current).

@@ -423,3 +423,26 @@ def test_forward_workspace_is_linear_in_the_clouds(lib):
         assert ws <= 8 * B * (N + M) + 512
         bw = lib.cd_backward_workspace_bytes(B, N, M)
         assert bw > 0 and bw % 256 == 0, (B, N, M, bw)
+
+
+def test_best_forward_workspace(lib):
+    # The pruned search's workspace: what cd_workspace_bytes needs or more, a
+    # multiple of 256, more exactly where the pairs pass 7e8 in clouds of 1800
+    # points or more, and never more than 4 GiB above which all pairs are taken.
+    lib.cd_workspace_bytes_best.restype = ctypes.c_size_t
+    lib.cd_workspace_bytes_best.argtypes = [ctypes.c_int64] * 3
+    import random
+    rng = random.Random(6)
+    shapes = [(16, 16384, 16384), (8, 65536, 65536), (4, 100000, 10000), (1, 30000, 25001),
+              (1, 1024, 1024), (32, 2048, 2048), (1, 300000, 1), (1, 2 ** 21, 2 ** 21),
+              (1, 2 ** 21 + 1, 2 ** 21), (1, 2 ** 30, 2 ** 30), (500, 2 ** 20, 2 ** 20)]
+    shapes += [(rng.randint(1, 64), rng.randint(1, 70000), rng.randint(1, 70000)) for _ in range(300)]
+    for B, N, M in shapes:
+        need, best = lib.cd_workspace_bytes(B, N, M), lib.cd_workspace_bytes_best(B, N, M)
+        pruned = (B * N * M >= 7e8 and min(N, M) >= 1800 and max(N, M) <= 2 ** 21
+                  and B * (N + M) <= 6e7)
+        if B * (N + M) <= 6e7 or max(N, M) > 2 ** 21:
+            assert (best > need) == pruned, (B, N, M, need, best)
+        assert best >= need and best % 256 == 0 and (best == need or best <= 4 << 30)
+    for B, N, M in ((0, 10, 10), (1, 0, 10), (-1, 10, 10), (2, 2 ** 30, 2 ** 30)):
+        assert lib.cd_workspace_bytes_best(B, N, M) == 0

@@ -1,0 +1,145 @@
+"""The pruned nearest-neighbour search (cd_forward with the larger workspace)
+against the all-pairs search of the same call, bitwise: distances and indices
+of both directions.  Sizes around the sort's chunks, ranges and nodes, clouds
+that strain it (equal points, outliers, lines, ties, one cloud far from the
+other), the static-workspace entry point, and a captured call."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+import gpu_checks as gc
+import oracle
+import paper_1911_05063_amd as cd
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _call(X, Y, ws_bytes):
+    B, N, M = X.shape[0], X.shape[1], Y.shape[1]
+    lib = cd.library()
+    # Workspace and outputs start as garbage that would show: small distances.
+    ws = torch.zeros(ws_bytes, dtype=torch.uint8, device=X.device)
+    out = [torch.full((B, n), -1, dtype=t, device=X.device)
+           for n in (N, M) for t in (torch.float32, torch.int32)]
+    st = lib.cd_forward(B, N, M, *[ctypes.c_void_p(t.data_ptr()) for t in [X, Y] + out],
+                        ctypes.c_void_p(ws.data_ptr()), ws_bytes,
+                        ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert st == 0, lib.cd_last_error()
+    return out
+
+
+def _compare(X, Y, what):
+    B, N, M = X.shape[0], X.shape[1], Y.shape[1]
+    need, best = cd.workspace_bytes(B, N, M), cd.workspace_bytes_best(B, N, M)
+    assert best > need, f"{what}: not a shape of the pruned search"
+    print(f"[tree] {what} B={B} N={N} M={M}", flush=True)
+    ref, got = _call(X, Y, need), _call(X, Y, best)
+    for name, a, b in zip(("dist_xy", "idx_xy", "dist_yx", "idx_yx"), got, ref):
+        assert torch.equal(a, b), f"{what} {name}: {int((a != b).sum())} differ"
+    return got
+
+
+# One range (<= 4096 points) against many, chunk and node remainders, B that
+# does and does not divide the 8 XCDs, more than 64 nodes.
+@pytest.mark.parametrize("kind,B,N,M", [
+    ("uniform", 1, 27000, 27001), ("sphere", 3, 16384, 16385), ("mesh", 16, 8193, 8191),
+    ("gmm", 2, 2049, 190000), ("grid_dup", 5, 40961, 4097), ("mesh", 64, 4096, 4095),
+    ("uniform", 1, 262145, 3071), ("gmm", 7, 10240, 12289)])
+def test_sizes_match_all_pairs(kind, B, N, M):
+    X, Y = synth.generate(kind, B, N, M, 7 * N + M)
+    _compare(gc.to_gpu(X), gc.to_gpu(Y), kind)
+
+
+def _strain(name):
+    rng = np.random.default_rng(11)
+    N, M = 30011, 28000
+    X, Y = rng.uniform(-1, 1, (1, N, 3)), rng.uniform(-1, 1, (1, M, 3))
+    if name == "all_equal":           # every target ties: the lowest index wins
+        X[:] = 0.25
+    elif name == "both_equal":
+        X[:], Y[:] = 0.25, -0.5
+    elif name == "few_places":        # thousands of copies of 40 points, zero distances
+        p = rng.uniform(-1, 1, (40, 3))
+        X[0], Y[0] = p[rng.integers(0, 40, N)], p[rng.integers(0, 40, M)]
+    elif name == "outliers":          # a thousandth of the points far away
+        X[0, ::1000] *= 1e4
+        Y[0, 500::1000] *= -1e6
+    elif name == "line":              # two coordinates constant
+        X[..., 1:], Y[..., 1:] = 0.0, 1e-3
+    elif name == "far_apart":         # all targets about as far
+        Y += 50.0
+    elif name == "shell":             # queries inside a sphere of targets
+        X = 0.3 * X
+        Y /= np.linalg.norm(Y, axis=2, keepdims=True)
+    elif name == "lattice":           # exact ties everywhere
+        X, Y = np.round(X * 16) / 16, np.round(Y * 16) / 16 + 1 / 32
+    elif name == "tiny":              # distances in float32's subnormal range
+        X, Y = X * 1e-21, Y * 1e-21
+    elif name == "huge":              # squared distances near float32's largest
+        X, Y = X * 3e18, Y * 3e18
+    return X.astype(np.float32), Y.astype(np.float32)
+
+
+@pytest.mark.parametrize("name", ["all_equal", "both_equal", "few_places", "outliers", "line",
+                                  "far_apart", "shell", "lattice", "tiny", "huge"])
+def test_strained_clouds_match_all_pairs(name):
+    X, Y = _strain(name)
+    _compare(gc.to_gpu(X), gc.to_gpu(Y), name)
+
+
+def test_entry_points_take_the_same_path_and_bits():
+    # Through the binding (default workspace), the static workspace and a graph.
+    X_np, Y_np = synth.generate("mesh", 2, 20000, 18001, 5)
+    X, Y = gc.to_gpu(X_np), gc.to_gpu(Y_np)
+    ref = _compare(X, Y, "entry points")
+    rows = np.stack([np.arange(64) % 2, np.arange(64) * 281], axis=1)
+    rd, ri = gc.sample_nn(X_np, Y_np, rows)
+    assert np.array_equal(gc.to_np(ref[0])[rows[:, 0], rows[:, 1]], rd)
+    assert np.array_equal(gc.to_np(ref[1])[rows[:, 0], rows[:, 1]], ri)
+    ws = torch.empty(cd.workspace_bytes_best(2, 20000, 18001), dtype=torch.uint8, device="cuda:0")
+    small = torch.empty(cd.workspace_bytes(2, 20000, 18001), dtype=torch.uint8, device="cuda:0")
+    for got in (cd.nn_distance(X, Y), cd.nn_distance(X, Y, ws), cd.nn_distance(X, Y, small),
+                cd.nn_distance_noalloc(X, Y)):
+        assert all(torch.equal(a, b) for a, b in zip(got, ref))
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(s):
+        cd.nn_distance(X, Y, ws)
+    torch.cuda.current_stream().wait_stream(s)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        out = cd.nn_distance(X, Y, ws)
+    for _ in range(3):
+        g.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(out, ref))
+        cd.nn_distance(Y, X)          # eager work in between
+        torch.cuda.synchronize()
+
+
+def test_many_clouds_on_two_streams():
+    # Each call has its own workspace: interleaved calls give each one's bits.
+    clouds = [tuple(gc.to_gpu(a) for a in synth.generate(k, B, N, M, 3))
+              for k, B, N, M in (("gmm", 4, 16000, 15000), ("sphere", 48, 4500, 4000))]
+    ref = [cd.nn_distance(X, Y) for X, Y in clouds]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    out = []
+    for _ in range(3):
+        for k, (X, Y) in enumerate(clouds):
+            with torch.cuda.stream(streams[k]):
+                out.append((k, cd.nn_distance(X, Y)))
+    torch.cuda.synchronize()
+    for k, got in out:
+        assert all(torch.equal(a, b) for a, b in zip(got, ref[k]))
+
+
+@pytest.mark.parametrize("B,N,M", [(1, 30000, 25001), (32, 8192, 8192)])
+def test_distances_match_the_oracle(B, N, M):
+    X, Y = synth.generate("mesh", B, N, M, 9)
+    got = _compare(gc.to_gpu(X), gc.to_gpu(Y), "oracle")
+    ref = oracle.nn(X[:2], Y[:2], fused=True)
+    gc.assert_nn_bitwise(tuple(gc.to_np(t)[:2] for t in got), ref, "tree")
