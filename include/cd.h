@@ -286,11 +286,18 @@ cd_status cd_mesh_sample_backward(int64_t B, int64_t nv, int64_t nf, const int32
  * serves both); 0 for sizes the checks reject. */
 size_t cd_p2s_workspace_bytes(int64_t B, int64_t S, int64_t nv, int64_t nf);
 
+/* Bytes of device workspace with which cd_p2s_forward takes its fastest path:
+ * cd_p2s_workspace_bytes, or more where sorting points and faces to skip far
+ * faces is faster than all pairs (from about 1.5e8 pairs and 2048 faces on).  The
+ * results are the same bits either way. */
+size_t cd_p2s_workspace_bytes_best(int64_t B, int64_t S, int64_t nv, int64_t nf);
+
 /*
  * dist [B, S] float32: squared distance from each point to the nearest face,
  * evaluated in float32; fidx [B, S] int32: that face, the lowest index among
  * exactly equal float32 distances; +inf and -1 when every face is ignored.
- * ws: cd_p2s_workspace_bytes(B, S, nv, nf) bytes, 256-byte aligned.
+ * ws: cd_p2s_workspace_bytes(B, S, nv, nf) bytes, 256-byte aligned; with
+ * cd_p2s_workspace_bytes_best(B, S, nv, nf) or more the fastest path is taken.
  */
 cd_status cd_p2s_forward(int64_t B, int64_t S, int64_t nv, int64_t nf, const float *P,
                          const float *V, const int32_t *F, float *dist, int32_t *fidx, void *ws,

@@ -93,6 +93,8 @@ def library() -> ctypes.CDLL:
                                             ctypes.c_size_t, vp]
     lib.cd_p2s_workspace_bytes.restype = ctypes.c_size_t
     lib.cd_p2s_workspace_bytes.argtypes = [i64, i64, i64, i64]
+    lib.cd_p2s_workspace_bytes_best.restype = ctypes.c_size_t
+    lib.cd_p2s_workspace_bytes_best.argtypes = [i64, i64, i64, i64]
     lib.cd_p2s_forward.restype = st
     lib.cd_p2s_forward.argtypes = [i64, i64, i64, i64, vp, vp, vp, vp, vp, vp, ctypes.c_size_t, vp]
     lib.cd_p2s_backward.restype = st
@@ -495,7 +497,8 @@ def p2s_forward(P, V, F):
     B, S, nv, nf = P.shape[0], P.shape[1], V.shape[1], F.shape[1]
     dist = torch.empty((B, S), dtype=torch.float32, device=P.device)
     fidx = torch.empty((B, S), dtype=torch.int32, device=P.device)
-    ws = _p2s_ws(B, S, nv, nf, P.device)
+    need = int(library().cd_p2s_workspace_bytes_best(B, S, nv, nf))
+    ws = torch.empty(max(need, 1), dtype=torch.uint8, device=P.device)
     with torch.cuda.device(P.device):
         _check(library().cd_p2s_forward(B, S, nv, nf, _ptr(P), _ptr(V), _ptr(F), _ptr(dist),
                                         _ptr(fidx), _ptr(ws), ws.numel(),

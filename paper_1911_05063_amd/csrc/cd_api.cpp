@@ -90,8 +90,7 @@ size_t cd_workspace_bytes_best(int64_t B, int64_t N, int64_t M)
 {
     const size_t need = cd_workspace_bytes(B, N, M);
     if (need == 0) return 0;
-    const cdk::TreePlan tree = cdk::plan_tree(B, N, M);
-    return tree.use ? std::max(need, tree.bytes) : need;
+    return std::max(need, cdk::tree_workspace_bytes(B, N, M));
 }
 
 cd_status cd_forward(int64_t B, int64_t N, int64_t M, const float *X, const float *Y,
@@ -112,10 +111,9 @@ cd_status cd_forward(int64_t B, int64_t N, int64_t M, const float *X, const floa
     if (!aligned256(ws)) return invalid("workspace not 256-byte aligned");
     if (cdk::forward_tiles(plan) > 2147483647LL) return invalid("too many tiles for one launch");
     const cdk::FwdArgs args{X, Y, dist_xy, idx_xy, dist_yx, idx_yx, ws};
-    const cdk::TreePlan tree = cdk::plan_tree(B, N, M);
-    const hipError_t e = tree.use && ws_bytes >= tree.bytes
-                             ? cdk::launch_tree(tree, N, M, args, stream)
-                             : cdk::launch_forward(plan, args, stream);
+    const size_t tree = cdk::tree_workspace_bytes(B, N, M);
+    const hipError_t e = tree > 0 && ws_bytes >= tree ? cdk::launch_tree(B, N, M, args, stream)
+                                                      : cdk::launch_forward(plan, args, stream);
     if (e != hipSuccess) return hip_failed(e, "cd_forward launch");
     return CD_OK;
 }
@@ -145,9 +143,9 @@ cd_status cd_forward_noalloc(int64_t B, int64_t N, int64_t M, const float *X, co
     hipError_t e = cdk::forward_scratch(stream, &ws);
     if (e != hipSuccess) return hip_failed(e, "cd_forward_noalloc scratch address");
     const cdk::FwdArgs args{X, Y, dist_xy, idx_xy, dist_yx, idx_yx, ws};
-    const cdk::TreePlan tree = cdk::plan_tree(B, N, M);
-    e = tree.use && tree.bytes <= cdk::kForwardScratchBytes ? cdk::launch_tree(tree, N, M, args, stream)
-                                                            : cdk::launch_forward(plan, args, stream);
+    const size_t tree = cdk::tree_workspace_bytes(B, N, M);
+    e = tree > 0 && tree <= cdk::kForwardScratchBytes ? cdk::launch_tree(B, N, M, args, stream)
+                                                      : cdk::launch_forward(plan, args, stream);
     if (e != hipSuccess) return hip_failed(e, "cd_forward_noalloc launch");
     return CD_OK;
 }
@@ -366,6 +364,14 @@ size_t cd_p2s_workspace_bytes(int64_t B, int64_t S, int64_t nv, int64_t nf)
     return (cdk::p2s_workspace_bytes(B, S, nv, nf) + 255) & ~static_cast<size_t>(255);
 }
 
+size_t cd_p2s_workspace_bytes_best(int64_t B, int64_t S, int64_t nv, int64_t nf)
+{
+    const size_t need = cd_p2s_workspace_bytes(B, S, nv, nf);
+    const size_t tree = need == 0 ? 0 : cdk::p2s_tree_bytes(B, S, nf);
+    // More than `need`, which asks for all pairs.
+    return tree == 0 ? need : std::max(need + 256, tree);
+}
+
 cd_status cd_p2s_forward(int64_t B, int64_t S, int64_t nv, int64_t nf, const float *P,
                          const float *V, const int32_t *F, float *dist, int32_t *fidx, void *ws,
                          size_t ws_bytes, hipStream_t stream)
@@ -374,9 +380,13 @@ cd_status cd_p2s_forward(int64_t B, int64_t S, int64_t nv, int64_t nf, const flo
     if (s != CD_OK) return s;
     if (B == 0 || S == 0) return CD_OK;
     if (!P || !V || !F || !dist || !fidx) return invalid("NULL array pointer");
-    s = check_ws(cd_p2s_workspace_bytes(B, S, nv, nf), ws, ws_bytes);
+    const size_t need = cd_p2s_workspace_bytes(B, S, nv, nf);
+    s = check_ws(need, ws, ws_bytes);
     if (s != CD_OK) return s;
-    const hipError_t e = cdk::launch_p2s_forward(B, S, nv, nf, P, V, F, dist, fidx, ws, stream);
+    const size_t best = cd_p2s_workspace_bytes_best(B, S, nv, nf);
+    const hipError_t e = best > need && ws_bytes >= best
+                             ? cdk::launch_p2s_tree(B, S, nv, nf, P, V, F, dist, fidx, ws, stream)
+                             : cdk::launch_p2s_forward(B, S, nv, nf, P, V, F, dist, fidx, ws, stream);
     if (e != hipSuccess) return hip_failed(e, "cd_p2s_forward launch");
     return CD_OK;
 }

@@ -41,17 +41,10 @@ int64_t forward_tiles(const FwdPlan &plan);
 
 hipError_t launch_forward(const FwdPlan &plan, const FwdArgs &args, hipStream_t stream);
 
-// Pruned search (nn_tree.hip): the same results from sorted clouds.
-struct TreePlan {
-    bool use;            // the shape gains from it
-    int64_t B;
-    bool bucket;         // some cloud has several ranges
-    int32_t ranges[2], log_c[2], chunks[2], nodes[2];
-    size_t entries[2], offs[2], curve[2], rec[2], leaf[2], node[2], list, bytes;   // workspace offsets and size
-};
-TreePlan plan_tree(int64_t B, int64_t N, int64_t M);
-hipError_t launch_tree(const TreePlan &plan, int64_t N, int64_t M, const FwdArgs &args,
-                       hipStream_t stream);
+// Pruned search over sorted clouds (nn_tree.hip): the same results.  The
+// workspace it needs, or 0 for a shape that gains nothing from it.
+size_t tree_workspace_bytes(int64_t B, int64_t N, int64_t M);
+hipError_t launch_tree(int64_t B, int64_t N, int64_t M, const FwdArgs &args, hipStream_t stream);
 
 // The no-allocation forward's workspace: a static device array of this many
 // bytes per GPU.  forward_scratch() gives its address on the device of
@@ -126,6 +119,13 @@ hipError_t launch_p2s_forward(int64_t B, int64_t S, int64_t nv, int64_t nf, cons
 hipError_t launch_p2s_backward(int64_t B, int64_t S, int64_t nv, int64_t nf, const float *P,
                                const float *V, const int32_t *F, const int32_t *fidx,
                                const float *g, float *gP, float *gV, void *ws, hipStream_t stream);
+
+// Pruned search over sorted points and faces (p2s_tree.hip): the same results.
+// The workspace it needs, or 0 for a shape that gains nothing from it.
+size_t p2s_tree_bytes(int64_t B, int64_t S, int64_t nf);
+hipError_t launch_p2s_tree(int64_t B, int64_t S, int64_t nv, int64_t nf, const float *P,
+                           const float *V, const int32_t *F, float *dist, int32_t *fidx, void *ws,
+                           hipStream_t stream);
 
 // Approximate Earth-mover's distance (emd.hip): scheduled log-domain Sinkhorn.
 size_t emd_workspace_bytes(int64_t B, int64_t N, int64_t M);

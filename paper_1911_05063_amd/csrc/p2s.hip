@@ -36,14 +36,11 @@
 
 #include "cd_internal.h"
 #include "mesh_common.h"
+#include "p2s_face.h"
 
 namespace cdk {
 namespace {
 
-constexpr int kRec = 32;          // floats per face record (31 used)
-// Corner of a face with a vertex index out of range: every distance to such a
-// record overflows to +inf (no inf - inf anywhere), so it is never chosen.
-constexpr float kFar = 3.0e38f;
 constexpr int kPQ = 8;            // points per lane
 constexpr int kPWaves = 4;
 constexpr int kPThreads = kPWaves * kWave;
@@ -79,82 +76,17 @@ __global__ __launch_bounds__(kThreads) void face_record_kernel(int64_t B, int64_
     const int32_t t[3] = {F[3 * k], F[3 * k + 1], F[3 * k + 2]};
     const bool ok = face_ok_nb(t, nv);
     const float *Vb = V + b * nv * 3;
-    double A[3], Bv[3], C[3], e0[3], e1[3], e2[3], n[3];
+    double A[3], Bv[3], C[3];
     for (int i = 0; i < 3; ++i) {
         A[i] = Vb[3 * static_cast<int64_t>(ok ? t[0] : 0) + i];
         Bv[i] = Vb[3 * static_cast<int64_t>(ok ? t[1] : 0) + i];
         C[i] = Vb[3 * static_cast<int64_t>(ok ? t[2] : 0) + i];
     }
     float *r = rec + k * kRec;
-    if (!ok) {
-        for (int i = 0; i < kRec; ++i) r[i] = 0.0f;
-        r[0] = r[1] = r[2] = kFar;
-        r[12] = __builtin_inff();
-        return;
-    }
-    for (int i = 0; i < 3; ++i) {
-        e0[i] = Bv[i] - A[i];
-        e1[i] = C[i] - A[i];
-        e2[i] = C[i] - Bv[i];
-    }
-    n[0] = e0[1] * e1[2] - e0[2] * e1[1];
-    n[1] = e0[2] * e1[0] - e0[0] * e1[2];
-    n[2] = e0[0] * e1[1] - e0[1] * e1[0];
-    const double nn = n[0] * n[0] + n[1] * n[1] + n[2] * n[2];
-    // Dual basis: g0 = (e1 x n) / |n|^2, g1 = (n x e0) / |n|^2, so that
-    // e0.g0 = e1.g1 = 1 and e1.g0 = e0.g1 = n.g0 = n.g1 = 0.
-    double g0[3] = {0, 0, 0}, g1[3] = {0, 0, 0}, nh[3] = {0, 0, 0};
-    const bool flat = !(nn > 0.0) || !std::isfinite(nn);
-    // One reciprocal per denominator (double divisions are long instruction
-    // sequences); the record is rounded to float32 afterwards.
-    if (!flat) {
-        const double rn = 1.0 / nn;
-        g0[0] = (e1[1] * n[2] - e1[2] * n[1]) * rn;
-        g0[1] = (e1[2] * n[0] - e1[0] * n[2]) * rn;
-        g0[2] = (e1[0] * n[1] - e1[1] * n[0]) * rn;
-        g1[0] = (n[1] * e0[2] - n[2] * e0[1]) * rn;
-        g1[1] = (n[2] * e0[0] - n[0] * e0[2]) * rn;
-        g1[2] = (n[0] * e0[1] - n[1] * e0[0]) * rn;
-        const double inv = 1.0 / sqrt(nn);
-        for (int i = 0; i < 3; ++i) nh[i] = n[i] * inv;
-    }
-    const double l0 = e0[0] * e0[0] + e0[1] * e0[1] + e0[2] * e0[2];
-    const double l1 = e1[0] * e1[0] + e1[1] * e1[1] + e1[2] * e1[2];
-    const double l2 = e2[0] * e2[0] + e2[1] * e2[1] + e2[2] * e2[2];
-    const double r0 = l0 > 0.0 ? 1.0 / l0 : 0.0;
-    const double r1 = l1 > 0.0 ? 1.0 / l1 : 0.0;
-    const double r2 = l2 > 0.0 ? 1.0 / l2 : 0.0;
-    for (int i = 0; i < 3; ++i) {
-        r[0 + i] = static_cast<float>(A[i]);
-        r[3 + i] = static_cast<float>(g0[i]);
-        r[6 + i] = static_cast<float>(g1[i]);
-        r[9 + i] = static_cast<float>(nh[i]);
-        r[13 + i] = static_cast<float>(e0[i]);
-        r[16 + i] = static_cast<float>(e0[i] * r0);
-        r[19 + i] = static_cast<float>(e1[i]);
-        r[22 + i] = static_cast<float>(e1[i] * r1);
-        r[25 + i] = static_cast<float>(e2[i]);
-        r[28 + i] = static_cast<float>(e2[i] * r2);
-    }
-    r[12] = flat ? __builtin_inff() : 0.0f;
-    r[31] = 0.0f;
-}
-
-__device__ __forceinline__ float fmaf_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-
-__device__ __forceinline__ float dot3(float x, float y, float z, float a, float b, float c)
-{
-    return fmaf_(z, c, fmaf_(y, b, x * a));
-}
-
-// Squared distance from v (relative to the segment's origin) to the segment
-// {sigma e : sigma in [0, 1]}, en = e / |e|^2.
-__device__ __forceinline__ float seg2(float vx, float vy, float vz, float ex, float ey, float ez,
-                                      float nx, float ny, float nz)
-{
-    const float sg = __builtin_amdgcn_fmed3f(dot3(vx, vy, vz, nx, ny, nz), 0.0f, 1.0f);
-    const float wx = fmaf_(-sg, ex, vx), wy = fmaf_(-sg, ey, vy), wz = fmaf_(-sg, ez, vz);
-    return dot3(wx, wy, wz, wx, wy, wz);
+    if (ok)
+        face_record(A, Bv, C, r);
+    else
+        far_record(r);
 }
 
 __global__ __launch_bounds__(kPThreads) void p2s_search_kernel(P2SArgs a)
@@ -203,27 +135,10 @@ __global__ __launch_bounds__(kPThreads) void p2s_search_kernel(P2SArgs a)
     __syncthreads();
     for (int32_t f = f0; f < f1; ++f) {
         const float4 *r4 = lrec + (f - f0) * (kRec / 4);
-        const float4 A0 = r4[0], A1 = r4[1], A2 = r4[2], A3 = r4[3], A4 = r4[4], A5 = r4[5], A6 = r4[6], A7 = r4[7];
-        const float ax = A0.x, ay = A0.y, az = A0.z;
-        const float g0x = A0.w, g0y = A1.x, g0z = A1.y;
-        const float g1x = A1.z, g1y = A1.w, g1z = A2.x;
-        const float nx = A2.y, ny = A2.z, nz = A2.w, cin = A3.x;
-        const float e0x = A3.y, e0y = A3.z, e0z = A3.w, n0x = A4.x, n0y = A4.y, n0z = A4.z;
-        const float e1x = A4.w, e1y = A5.x, e1z = A5.y, n1x = A5.z, n1y = A5.w, n1z = A6.x;
-        const float e2x = A6.y, e2y = A6.z, e2z = A6.w, n2x = A7.x, n2y = A7.y, n2z = A7.z;
+        const float4 R[8] = {r4[0], r4[1], r4[2], r4[3], r4[4], r4[5], r4[6], r4[7]};
 #pragma unroll
         for (int k = 0; k < kPQ; ++k) {
-            const float vx = px[k] - ax, vy = py[k] - ay, vz = pz[k] - az;
-            const float s = dot3(vx, vy, vz, g0x, g0y, g0z);
-            const float t = dot3(vx, vy, vz, g1x, g1y, g1z);
-            const float h = dot3(vx, vy, vz, nx, ny, nz);
-            const float u = (1.0f - s) - t;
-            const bool inside = __builtin_fminf(__builtin_fminf(s, t), u) >= cin;
-            const float dab = seg2(vx, vy, vz, e0x, e0y, e0z, n0x, n0y, n0z);
-            const float dca = seg2(vx, vy, vz, e1x, e1y, e1z, n1x, n1y, n1z);
-            const float dbc = seg2(vx - e0x, vy - e0y, vz - e0z, e2x, e2y, e2z, n2x, n2y, n2z);
-            const float edge = __builtin_fminf(__builtin_fminf(dab, dca), dbc);
-            const float d = inside ? h * h : edge;
+            const float d = face_dist(px[k], py[k], pz[k], R);
             if (d < best[k]) {
                 best[k] = d;
                 bidx[k] = f;

@@ -24,6 +24,8 @@
 // (lo = +inf, hi = -inf).
 #pragma once
 
+#include <algorithm>
+
 #include "cd_internal.h"
 #include "fixed_point.h"
 
@@ -33,21 +35,6 @@ constexpr int kLeaf = 16;
 constexpr int kNodeLeaves = 64;
 constexpr int kNode = kLeaf * kNodeLeaves;
 constexpr int kTile = 64;                        // queries of a search wave
-constexpr int kBucketThreads = 256;
-constexpr int kBucketHeld = 8;                   // points per thread
-constexpr int kSortChunk = kBucketThreads * kBucketHeld;
-constexpr int kSortSamples = 4 * kBucketThreads;
-constexpr int kRangeLevels = 4;                  // curve levels that tell ranges apart
-constexpr int kRangeCells = 1 << (3 * kRangeLevels);
-constexpr int kMaxRanges = 512;                  // per cloud
-constexpr int kSortThreads = 512;
-constexpr int kSortWaves = kSortThreads / kWave;
-constexpr int kSortHeld = 8;                     // points per thread kept in registers
-constexpr int kOneRange = kSortHeld * kSortThreads;   // clouds up to this size: one range
-constexpr int kRangePoints = 1536;               // points per range aimed at above that
-constexpr int kMaxChunks = 1024;                 // per cloud (LDS segment table)
-constexpr int kLogCells = 13;                    // cells per range at most: 32 KB of LDS counters
-constexpr int kLevels = 10;                      // curve levels within a range
 constexpr uint32_t kNoPoint = 0xffffffffu;       // index of a slot without a point
 constexpr float kFarAway = 3.0e38f;              // its x: every squared distance to it is +inf
 
@@ -63,13 +50,37 @@ struct SortShape {
     int32_t n;
     int32_t ranges;
     int32_t log_c;      // log2(cells per range)
-    int32_t chunks;     // of kSortChunk points
+    int32_t chunks;     // of the bucket pass
     int32_t nodes;      // nodes stored (slots / kNode)
 };
 
-struct P3f {
-    float x, y, z;
+// The sorted clouds of a batch in a workspace (byte offsets from its start).
+struct SortPlan {
+    SortShape s;
+    int64_t B;
+    size_t entries, offs, curve, rec, leaf, node;
 };
+
+// A batch of clouds to sort, and where to.
+struct SortJob {
+    const float *P;         // [B, n, 3]
+    float4 *rec;            // [B, nodes kNode] records
+    Box *leaf, *node;       // [B, nodes kNodeLeaves], [B, nodes]
+    float4 *entries;        // bucket pass: [B, chunks, points of a chunk],
+    uint32_t *offs;         // [B, chunks, ranges + 1],
+    struct Curve *curve;    // [B]
+    SortShape s;
+};
+
+// Clouds of at most this many points can be sorted.
+constexpr int64_t kSortMaxPoints = int64_t{1} << 21;
+
+// Lays the sorted clouds out from byte `at` on, which it moves past them.
+SortPlan plan_sort(int64_t B, int64_t n, size_t &at);
+SortJob sort_job(const SortPlan &p, const float *P, char *ws);
+// Sorts two batches of B clouds in the same launches and zeroes *counter.
+hipError_t launch_sort(int64_t B, const SortJob &a, const SortJob &b, uint32_t *counter,
+                       hipStream_t stream);
 
 template <int kCtrl>
 __device__ __forceinline__ uint32_t dpp_u32(uint32_t v)
@@ -105,392 +116,205 @@ __device__ __forceinline__ uint32_t wave_min_u32(uint32_t m)
     return min(r32[0], r32[1]);
 }
 
-// Inclusive prefix sum over the wave in lane order.
-__device__ __forceinline__ uint32_t wave_scan_u32(uint32_t v)
+constexpr uint32_t kXcds = 8;       // accelerator complex dies of an MI355X
+
+// Consecutive workgroups on one XCD (they are dealt out round-robin): the
+// ranges and tiles of one item share one L2.
+__device__ __forceinline__ uint32_t xcd_block()
 {
-    const auto step = [](uint32_t x, int moved) { return x + static_cast<uint32_t>(moved); };
-    v = step(v, __builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x111, 0xF, 0xF, false));
-    v = step(v, __builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x112, 0xF, 0xF, false));
-    v = step(v, __builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x114, 0xF, 0xF, false));
-    v = step(v, __builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x118, 0xF, 0xF, false));
-    v = step(v, __builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x142, 0xA, 0xF, false));
-    v = step(v, __builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x143, 0xC, 0xF, false));
-    return v;
+    const uint32_t i = blockIdx.x, per = gridDim.x / kXcds;
+    return i < kXcds * per ? (i % kXcds) * per + i / kXcds : i;
 }
 
-// Index along the Hilbert curve of a cell of the 2^kLevels cube (kLevels bits
-// per axis), after Skilling, "Programming the Hilbert curve" (2004): the axes
-// are turned level by level, then Gray-decoded and interleaved.  Neighbours on
-// the curve are neighbours in space, which curve index order is not at its jumps:
-// the searches visit about half as many leaves.
-template <int kLevels>
-__device__ __forceinline__ uint32_t hilbert(uint32_t x, uint32_t y, uint32_t z)
+__device__ __forceinline__ double pack(float d, uint32_t i)
 {
-#pragma unroll
-    for (int l = kLevels - 1; l > 0; --l) {
-        const uint32_t low = (1u << l) - 1u;
-        const auto bit = [&](uint32_t v) { return 0u - ((v >> l) & 1u); };   // all ones if set
-        // Axis bit set: invert x's lower bits; else swap x's and the axis' lower bits.
-        x ^= bit(x) & low;
-        uint32_t t = (x ^ y) & low & ~bit(y);
-        x ^= t ^ (bit(y) & low);
-        y ^= t;
-        t = (x ^ z) & low & ~bit(z);
-        x ^= t ^ (bit(z) & low);
-        z ^= t;
-    }
-    y ^= x;
-    z ^= y;
-    uint32_t t = 0u;
-#pragma unroll
-    for (int l = kLevels - 1; l > 0; --l) t ^= ((1u << l) - 1u) & (0u - ((z >> l) & 1u));
-    x ^= t;
-    y ^= t;
-    z ^= t;
-    uint32_t code = 0u;
-#pragma unroll
-    for (int l = kLevels - 1; l >= 0; --l)
-        code = code << 3 | ((x >> l) & 1u) << 2 | ((y >> l) & 1u) << 1 | ((z >> l) & 1u);
-    return code;
+    return __hiloint2double(__float_as_int(d), static_cast<int>(i));
 }
 
-// A box as maxima: -lo, hi.
-struct MaxBox {
-    float v[6];
-    __device__ __forceinline__ void clear()
-    {
-#pragma unroll
-        for (int c = 0; c < 6; ++c) v[c] = -__builtin_inff();
+__device__ __forceinline__ unsigned long long as_bits(double k)
+{
+    return static_cast<unsigned long long>(__double_as_longlong(k));
+}
+
+__device__ __forceinline__ double as_key(unsigned long long k)
+{
+    return __longlong_as_double(static_cast<long long>(k));
+}
+
+__device__ __forceinline__ double min_key(double a, double b)
+{
+    double r;
+    asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+
+// Smallest distance, per axis, from an interval to another (0 if they meet).
+__device__ __forceinline__ float gap(float alo, float ahi, float blo, float bhi)
+{
+    float r;
+    const float u = blo - ahi, v = alo - bhi;
+    asm("v_max3_f32 %0, %1, %2, 0" : "=v"(r) : "v"(u), "v"(v));
+    return r;
+}
+
+__device__ __forceinline__ float sum_sq(float x, float y, float z)
+{
+    return __builtin_fmaf(z, z, __builtin_fmaf(y, y, x * x));
+}
+
+__device__ __forceinline__ float bound(const float4 &alo, const float4 &ahi, const float4 &blo,
+                                       const float4 &bhi)
+{
+    return sum_sq(gap(alo.x, ahi.x, blo.x, bhi.x), gap(alo.y, ahi.y, blo.y, bhi.y),
+                  gap(alo.z, ahi.z, blo.z, bhi.z));
+}
+
+__device__ __forceinline__ float4 middle(const float4 &lo, const float4 &hi)
+{
+    return make_float4(0.5f * (lo.x + hi.x), 0.5f * (lo.y + hi.y), 0.5f * (lo.z + hi.z), 0.0f);
+}
+
+// The value lane U of each row of 16 holds, in all its lanes.
+template <int U>
+__device__ __forceinline__ float row_lane(float v)
+{
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x150 + U, 0xF, 0xF, true));
+}
+
+template <int U>
+__device__ __forceinline__ void leaf_keys(const float4 &q, const float4 &r, double (&k)[kLeaf])
+{
+    if constexpr (U < kLeaf) {
+        const float dx = row_lane<U>(r.x) - q.x;
+        const float dy = row_lane<U>(r.y) - q.y;
+        const float dz = row_lane<U>(r.z) - q.z;
+        k[U] = pack(sum_sq(dx, dy, dz), __float_as_uint(row_lane<U>(r.w)));
+        leaf_keys<U + 1>(q, r, k);
     }
-    __device__ __forceinline__ void add(float x, float y, float z)
-    {
-        v[0] = fmaxf(v[0], -x);
-        v[1] = fmaxf(v[1], -y);
-        v[2] = fmaxf(v[2], -z);
-        v[3] = fmaxf(v[3], x);
-        v[4] = fmaxf(v[4], y);
-        v[5] = fmaxf(v[5], z);
-    }
-    // Over the workgroup's waves (red: one entry each); ends with a barrier.
-    template <int kWaves>
-    __device__ __forceinline__ void group(float (*red)[6])
-    {
-#pragma unroll
-        for (int c = 0; c < 6; ++c) {
-            v[c] = wave_max(v[c]);
-            if (threadIdx.x % kWave == 0) red[threadIdx.x / kWave][c] = v[c];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int c = 0; c < 6; ++c) v[c] = wave_max(red[threadIdx.x % kWaves][c]);
-    }
+}
+
+__device__ __forceinline__ float high(double k) { return __int_as_float(__double2hiint(k)); }
+
+// Minimum with the lanes 16 and 32 apart: over the four rows.
+__device__ __forceinline__ double rows_min(double k)
+{
+    auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(k), __double2loint(k), false, false);
+    auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(k), __double2hiint(k), false, false);
+    k = min_key(__hiloint2double(hi[0], lo[0]), __hiloint2double(hi[1], lo[1]));
+    lo = __builtin_amdgcn_permlane32_swap(__double2loint(k), __double2loint(k), false, false);
+    hi = __builtin_amdgcn_permlane32_swap(__double2hiint(k), __double2hiint(k), false, false);
+    return min_key(__hiloint2double(hi[0], lo[0]), __hiloint2double(hi[1], lo[1]));
+}
+
+template <int kCtrl>
+__device__ __forceinline__ double dpp_key(double k)
+{
+    return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(k), kCtrl, 0xF, 0xF, true),
+                            __builtin_amdgcn_mov_dpp(__double2loint(k), kCtrl, 0xF, 0xF, true));
+}
+
+__device__ __forceinline__ float row_max(float w)
+{
+    w = fmaxf(w, dpp_f<0xB1>(w));
+    w = fmaxf(w, dpp_f<0x4E>(w));
+    w = fmaxf(w, dpp_f<0x141>(w));
+    return fmaxf(w, dpp_f<0x140>(w));
+}
+
+// A sorted cloud to search: its leaf and node boxes (two float4 each).
+struct Targets {
+    const float4 *leaf, *node;
+    uint32_t nodes;
 };
 
-// Curve indices in a box, 2^kLevels cells over its longest side, to any number
-// of levels (fewer levels give the leading bits).  Any value, NaN included,
-// gives an index.
-struct Curve {
-    float lo[3], scale;     // cells per unit at kLevels levels
-    Curve() = default;
-    __device__ __forceinline__ explicit Curve(const MaxBox &b)
-    {
-        lo[0] = -b.v[0];
-        lo[1] = -b.v[1];
-        lo[2] = -b.v[2];
-        const float ext = fmaxf(b.v[3] + b.v[0], fmaxf(b.v[4] + b.v[1], b.v[5] + b.v[2]));
-        scale = ext > 0.0f ? static_cast<float>(1 << kLevels) / ext : 0.0f;
-    }
-    template <int kTo>
-    __device__ __forceinline__ uint32_t code(float x, float y, float z) const
-    {
-        const auto cell = [&](float p, float l) {
-            return static_cast<uint32_t>(__builtin_amdgcn_fmed3f(
-                       (p - l) * scale, 0.0f, static_cast<float>((1 << kLevels) - 1))) >>
-                   (kLevels - kTo);
-        };
-        return hilbert<kTo>(cell(x, lo[0]), cell(y, lo[1]), cell(z, lo[2]));
-    }
-};
+constexpr int kNear = 4;    // nodes looked at for the first bounds (2: 118 -> 133 us on meshes)
 
-// Exclusive prefix sums over kPer kWave counters per wave of a workgroup of
-// kWaves waves, in place (all threads; total: one entry per wave); returns the
-// sum of all.  Starts and ends with a barrier.
-template <int kWaves, int kPer>
-__device__ __forceinline__ uint32_t scan_counters(uint32_t *cells, uint32_t *total)
+// The four leaves nearest to the box [qlo, qhi] (each the nearest of one
+// lane's) in the kNear nearest nodes; ~0: every distance overflows.  Order:
+// box distance, then that of the centres (boxes that meet are all at 0).
+// nlo, nhi: box of node min(lane, nodes - 1).
+__device__ __forceinline__ void nearest_leaves(const Targets &j, const float4 &qlo, const float4 &qhi,
+                                               const float4 &nlo, const float4 &nhi, uint32_t lane,
+                                               uint32_t near_leaf[4])
 {
-    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-    uint32_t *mine = cells + wave * kPer * kWave + lane;
-    __syncthreads();
-    uint32_t v[kPer], carry = 0u;
-#pragma unroll
-    for (int k = 0; k < kPer; ++k) v[k] = mine[k * kWave];
-#pragma unroll
-    for (int k = 0; k < kPer; ++k) {
-        const uint32_t incl = wave_scan_u32(v[k]);
-        v[k] = carry + incl - v[k];
-        carry += __builtin_amdgcn_readlane(incl, kWave - 1);
-    }
-    if (lane == 0) total[wave] = carry;
-    __syncthreads();
-    uint32_t before = 0u, all = 0u;
-#pragma unroll
-    for (int k = 0; k < kWaves; ++k) {
-        const uint32_t t = total[k];
-        before += k < wave ? t : 0u;
-        all += t;
-    }
-#pragma unroll
-    for (int k = 0; k < kPer; ++k) mine[k * kWave] = v[k] + before;
-    __syncthreads();
-    return all;
-}
-
-template <int kWaves>
-__device__ __forceinline__ uint32_t scan_counters(uint32_t *cells, int n, uint32_t *total)
-{
-    constexpr int kGroup = kWaves * kWave;
-    if (n <= kGroup) return scan_counters<kWaves, 1>(cells, total);
-    if (n <= 2 * kGroup) return scan_counters<kWaves, 2>(cells, total);
-    if (n <= 4 * kGroup) return scan_counters<kWaves, 4>(cells, total);
-    if (n <= 8 * kGroup) return scan_counters<kWaves, 8>(cells, total);
-    return scan_counters<kWaves, 16>(cells, total);
-}
-
-// Points of one chunk grouped by range: entries (x, y, z, index) and, per
-// range, the first of its entries (one more offset ends the last range).
-__device__ __forceinline__ void bucket_chunk(const P3f *__restrict__ pts, const SortShape &s,
-                                             int chunk, float4 *__restrict__ entries,
-                                             uint32_t *__restrict__ offs,
-                                             Curve *__restrict__ shared_curve)
-{
-    constexpr int kPerThread = kSortSamples / kBucketThreads;
-    __shared__ uint32_t share[kRangeCells];      // samples per cell, then its range
-    __shared__ uint32_t hist[kMaxRanges];
-    __shared__ float red[kBucketThreads / kWave][6];
-    __shared__ uint32_t total[kBucketThreads / kWave];
-    const int tid = threadIdx.x;
-    const int first = chunk * kSortChunk, last = s.n - 1;
-    P3f p[kBucketHeld], sample[kPerThread];
-#pragma unroll
-    for (int k = 0; k < kPerThread; ++k)
-        sample[k] = pts[static_cast<uint64_t>(k * kBucketThreads + tid) * static_cast<uint32_t>(last) /
-                        (kSortSamples - 1)];
-#pragma unroll
-    for (int k = 0; k < kBucketHeld; ++k) p[k] = pts[min(first + k * kBucketThreads + tid, last)];
-    for (int r = tid; r < kMaxRanges; r += kBucketThreads) hist[r] = 0u;
-    for (int r = tid; r < kRangeCells; r += kBucketThreads) share[r] = 0u;
-    MaxBox box;
-    box.clear();
-#pragma unroll
-    for (int k = 0; k < kPerThread; ++k) box.add(sample[k].x, sample[k].y, sample[k].z);
-    box.group<kBucketThreads / kWave>(red);
-    const Curve curve(box);
-    if (chunk == 0 && tid == 0) *shared_curve = curve;
-#pragma unroll
-    for (int k = 0; k < kPerThread; ++k)
-        atomicAdd(&share[curve.code<kRangeLevels>(sample[k].x, sample[k].y, sample[k].z)], 1u);
-    scan_counters<kBucketThreads / kWave>(share, kRangeCells, total);
-    // A cell whose samples follow t others belongs to range t ranges / samples.
-    // A cell of four ranges' worth of samples or more (many equal points) is
-    // dealt out by index: its points' order says nothing anyway.
-    uint32_t range[kBucketHeld], rank[kBucketHeld];
-#pragma unroll
-    for (int k = 0; k < kBucketHeld; ++k) {
-        const int i = first + k * kBucketThreads + tid;
-        const uint32_t c = curve.code<kRangeLevels>(p[k].x, p[k].y, p[k].z);
-        const uint32_t t = share[c], own = (c + 1 < kRangeCells ? share[c + 1] : kSortSamples) - t;
-        const uint32_t dealt = own * s.ranges >= 4 * kSortSamples
-                                   ? (static_cast<uint32_t>(i) * 2654435761u >> 16) * own >> 16 : 0u;
-        range[k] = min((t + dealt) * s.ranges / kSortSamples, static_cast<uint32_t>(s.ranges) - 1u);
-        if (i <= last) rank[k] = atomicAdd(&hist[range[k]], 1u);
-    }
-    scan_counters<kBucketThreads / kWave>(hist, s.ranges, total);
-    const uint32_t count = static_cast<uint32_t>(min(kSortChunk, s.n - first));
-#pragma unroll
-    for (int k = 0; k < kBucketHeld; ++k) {
-        const int i = first + k * kBucketThreads + tid;
-        if (i <= last)
-            entries[first + hist[range[k]] + rank[k]] =
-                make_float4(p[k].x, p[k].y, p[k].z, __uint_as_float(static_cast<uint32_t>(i)));
-    }
-    uint32_t *o = offs + static_cast<size_t>(chunk) * (s.ranges + 1);
-    for (int r = tid; r < s.ranges; r += kBucketThreads) o[r] = hist[r];
-    if (tid == 0) o[s.ranges] = count;
-}
-
-// Range w of one cloud.
-__device__ __forceinline__ void sort_range(const P3f *__restrict__ pts, const SortShape &s, int w,
-                                           const float4 *__restrict__ entries,
-                                           const uint32_t *__restrict__ offs,
-                                           const Curve *__restrict__ shared_curve,
-                                           float4 *__restrict__ rec, Box *__restrict__ leaf,
-                                           Box *__restrict__ node)
-{
-    __shared__ uint32_t cells[1 << kLogCells];
-    __shared__ uint32_t pre[kMaxChunks + 1], seg[kMaxChunks];
-    __shared__ float red[kSortWaves][6];
-    __shared__ uint32_t total[kSortWaves], below_total[kSortWaves], ends[kSortWaves][2];
-    const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
-    const int ncell = 1 << s.log_c, ranges = s.ranges;
-    const bool one = ranges == 1;
-    uint32_t count = static_cast<uint32_t>(s.n), below = 0u;
-    const int scanned = max(ncell, kSortThreads);
-    for (int c = tid; c < scanned; c += kSortThreads) cells[c] = 0u;
-    if (!one) {
-        // The range's segment of every chunk (two chunks per thread), the
-        // points before each, and the points of lower ranges.
-        uint32_t len[2], lower = 0u;
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            const int c = 2 * tid + k;
-            const uint32_t *o = offs + static_cast<size_t>(min(c, s.chunks - 1)) * (ranges + 1) + w;
-            const uint32_t a = o[0], e = o[1];
-            len[k] = c < s.chunks ? e - a : 0u;
-            lower += c < s.chunks ? a : 0u;
-            if (c < s.chunks) seg[c] = a;
-        }
-        const uint32_t incl = wave_scan_u32(len[0] + len[1]), li = wave_scan_u32(lower);
-        if (lane == kWave - 1) {
-            total[wave] = incl;
-            below_total[wave] = li;
-        }
-        __syncthreads();
-        uint32_t before = incl - len[0] - len[1];
-        count = 0u;
-#pragma unroll
-        for (int k = 0; k < kSortWaves; ++k) {
-            const uint32_t t = total[k];
-            before += k < wave ? t : 0u;
-            count += t;
-            below += below_total[k];
-        }
-        if (2 * tid < s.chunks) pre[2 * tid] = before;
-        if (2 * tid + 1 < s.chunks) pre[2 * tid + 1] = before + len[0];
-        if (tid == 0) pre[s.chunks] = count;
-        __syncthreads();
-    }
-    // Point i of the range.
-    const auto fetch = [&](uint32_t i) -> float4 {
-        if (one) {
-            const P3f p = pts[i];
-            return make_float4(p.x, p.y, p.z, __uint_as_float(i));
-        }
-        int lo = 0, hi = s.chunks;
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (pre[mid] <= i) lo = mid; else hi = mid;
-        }
-        return entries[static_cast<uint32_t>(lo) * kSortChunk + seg[lo] + (i - pre[lo])];
+    const float4 mid = middle(qlo, qhi);
+    const auto order = [&](const float4 &lo, const float4 &hi) {
+        const float4 m = middle(lo, hi);
+        return __float_as_uint(__builtin_fmaf(0.01f, sum_sq(mid.x - m.x, mid.y - m.y, mid.z - m.z),
+                                              bound(qlo, qhi, lo, hi)));
     };
-    const uint32_t start = (below + kNode - 1) / kNode * kNode + static_cast<uint32_t>(w) * kNode;
-    const uint32_t next = (below + count + kNode - 1) / kNode * kNode + static_cast<uint32_t>(w + 1) * kNode;
-    float4 *out = rec + start;
-    if (count > 0u) {
-        const bool held = count <= kSortHeld * kSortThreads;
-        float4 p[kSortHeld];
-        Curve curve;
-        if (held) {
-#pragma unroll
-            for (int k = 0; k < kSortHeld; ++k)
-                if (static_cast<uint32_t>(k * kSortThreads) < count)
-                    p[k] = fetch(min(static_cast<uint32_t>(k * kSortThreads + tid), count - 1));
-                else
-                    p[k] = p[0];
-        }
-        if (one) {
-            MaxBox box;
-            box.clear();
-            if (held) {
-#pragma unroll
-                for (int k = 0; k < kSortHeld; ++k) box.add(p[k].x, p[k].y, p[k].z);
-            } else {
-                for (uint32_t i = tid; i < count; i += kSortThreads) {
-                    const float4 q = fetch(i);
-                    box.add(q.x, q.y, q.z);
-                }
-            }
-            box.group<kSortWaves>(red);
-            curve = Curve(box);
-        } else {
-            curve = *shared_curve;
-        }
-        // The range's codes from the lowest on, in as many cells as there are.
-        uint32_t code[kSortHeld], rank[kSortHeld], low = kNoPoint, high = 0u;
-        if (held) {
-#pragma unroll
-            for (int k = 0; k < kSortHeld; ++k) {
-                if (static_cast<uint32_t>(k * kSortThreads) >= count) continue;
-                code[k] = curve.code<kLevels>(p[k].x, p[k].y, p[k].z);
-                low = min(low, code[k]);
-                high = max(high, code[k]);
-            }
-        } else {
-            for (uint32_t i = tid; i < count; i += kSortThreads) {
-                const float4 q = fetch(i);
-                const uint32_t c = curve.code<kLevels>(q.x, q.y, q.z);
-                low = min(low, c);
-                high = max(high, c);
-            }
-        }
-        low = wave_min_u32(low);
-        high = ~wave_min_u32(~high);
-        if (lane == 0) {
-            ends[wave][0] = low;
-            ends[wave][1] = ~high;
-        }
-        __syncthreads();
-        low = wave_min_u32(ends[lane % kSortWaves][0]);
-        high = ~wave_min_u32(ends[lane % kSortWaves][1]);
-        const int down = max(32 - __builtin_clz((high - low) | 1u) - s.log_c, 0);
-        if (held) {
-#pragma unroll
-            for (int k = 0; k < kSortHeld; ++k)
-                if (static_cast<uint32_t>(k * kSortThreads + tid) < count)
-                    rank[k] = atomicAdd(&cells[(code[k] - low) >> down], 1u);
-        } else {
-            for (uint32_t i = tid; i < count; i += kSortThreads) {
-                const float4 q = fetch(i);
-                atomicAdd(&cells[(curve.code<kLevels>(q.x, q.y, q.z) - low) >> down], 1u);
-            }
-        }
-        scan_counters<kSortWaves>(cells, scanned, total);
-        if (held) {
-#pragma unroll
-            for (int k = 0; k < kSortHeld; ++k)
-                if (static_cast<uint32_t>(k * kSortThreads + tid) < count) out[cells[(code[k] - low) >> down] + rank[k]] = p[k];
-        } else {
-            for (uint32_t i = tid; i < count; i += kSortThreads) {
-                const float4 q = fetch(i);
-                out[atomicAdd(&cells[(curve.code<kLevels>(q.x, q.y, q.z) - low) >> down], 1u)] = q;
-            }
-        }
-        const uint32_t filled = (count + kTile - 1) / kTile * kTile;
-        for (uint32_t t = count + tid; t < filled; t += kSortThreads)
-            out[t] = make_float4(kFarAway, 0.0f, 0.0f, __uint_as_float(kNoPoint));
-        __syncthreads();
+    uint32_t near = order(nlo, nhi), near_at = min(lane, j.nodes - 1);
+    for (uint32_t from = kWave; from < j.nodes; from += kWave) {
+        const uint32_t i = min(from + lane, j.nodes - 1);
+        const uint32_t k = order(j.node[2 * i], j.node[2 * i + 1]);
+        near_at = k < near ? i : near_at;
+        near = min(near, k);
     }
-    // Boxes: a wave takes a node, a lane a leaf.
-    for (uint32_t nd = start / kNode + wave; nd < next / kNode; nd += kSortWaves) {
-        const uint32_t r0 = nd * kNode + lane * kLeaf - start;   // first record of the leaf
-        MaxBox b;
-        b.clear();
-        uint32_t first = kNoPoint;
-        if (r0 < count) {
-            const uint32_t m = min(static_cast<uint32_t>(kLeaf), count - r0);
-            const float4 *src = out + r0;
+    near = (near & ~63u) | lane;
+    uint32_t nodes[kNear];
 #pragma unroll
-            for (uint32_t u = 0; u < kLeaf; ++u) {
-                const float4 q = src[min(u, m - 1)];
-                b.add(q.x, q.y, q.z);
-                first = min(first, __float_as_uint(q.w));
-            }
+    for (int v = 0; v < kNear; ++v) {
+        const uint32_t m = __builtin_amdgcn_readfirstlane(wave_min_u32(near));
+        nodes[v] = v == 0 || m < 0x7f800000u ? __builtin_amdgcn_readlane(near_at, m & 63u) : nodes[0];
+        near = lane == (m & 63u) ? kNoPoint : near;
+    }
+    uint32_t key = kNoPoint, key_at = 0u;
+#pragma unroll
+    for (int v = 0; v < kNear; ++v) {
+        const uint32_t at = nodes[v] * kNodeLeaves + lane;
+        const uint32_t k = order(j.leaf[at * 2], j.leaf[at * 2 + 1]);
+        key_at = k < key ? at : key_at;
+        key = min(key, k);
+    }
+    key = (key & ~63u) | lane;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const uint32_t m = __builtin_amdgcn_readfirstlane(wave_min_u32(key));
+        near_leaf[v] = m < 0x7f800000u ? __builtin_amdgcn_readlane(key_at, m & 63u)
+                                       : v > 0 ? near_leaf[0] : kNoPoint;
+        key = lane == (m & 63u) ? kNoPoint : key;
+    }
+}
+
+// Appends v of the lanes that take it to a list of n values in LDS.
+__device__ __forceinline__ void append(uint32_t *list, uint32_t &n, bool take, uint32_t v)
+{
+    const uint64_t taken = __ballot(take);
+    if (take)
+        list[__builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(taken >> 32),
+            __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(taken), n))] = v;
+    n += __popcll(taken);
+}
+
+// Queues the leaves, other than the four done, that takes(lo, hi) of their box
+// (and of their node's) lets pass.  full() is called when more than `limit` are
+// queued and ends the walk by returning false; it may empty the queue and
+// tighten what takes() lets pass.
+template <class Takes, class Full>
+__device__ __forceinline__ void gather(const Targets &j, const float4 &nlo, const float4 &nhi,
+                                       uint32_t lane, const uint32_t done[4], uint32_t *queue,
+                                       uint32_t &queued, uint32_t limit, const Takes &takes,
+                                       const Full &full)
+{
+    for (uint32_t from = 0; from < j.nodes; from += kWave) {
+        float4 lo = nlo, hi = nhi;
+        if (from > 0u) {
+            const uint32_t i = min(from + lane, j.nodes - 1);
+            lo = j.node[2 * i];
+            hi = j.node[2 * i + 1];
         }
-        leaf[static_cast<size_t>(nd) * kNodeLeaves + lane] =
-            Box{-b.v[0], -b.v[1], -b.v[2], first, b.v[3], b.v[4], b.v[5], 0u};
+        uint64_t left = ~0ull;
+        for (;;) {
+            left &= __ballot(from + lane < j.nodes && takes(lo, hi));
+            if (left == 0ull) break;
+            const uint32_t at = (from + __builtin_ctzll(left)) * kNodeLeaves + lane;
+            left &= left - 1ull;
+            bool take = takes(j.leaf[at * 2], j.leaf[at * 2 + 1]);
 #pragma unroll
-        for (int c = 0; c < 6; ++c) b.v[c] = wave_max(b.v[c]);
-        first = wave_min_u32(first);
-        if (lane == 0) node[nd] = Box{-b.v[0], -b.v[1], -b.v[2], first, b.v[3], b.v[4], b.v[5], 0u};
+            for (int v = 0; v < 4; ++v) take = take && done[v] != at;
+            append(queue, queued, take, at);
+            if (queued > limit && !full()) return;
+        }
     }
 }
 

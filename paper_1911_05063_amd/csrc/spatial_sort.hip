@@ -1,0 +1,518 @@
+// The sort of spatial_sort.h: kernels and launches.
+#include "spatial_sort.h"
+
+namespace cdk {
+
+namespace {
+
+constexpr int kBucketThreads = 256;
+constexpr int kBucketHeld = 8;                   // points per thread
+constexpr int kSortChunk = kBucketThreads * kBucketHeld;
+constexpr int kSortSamples = 4 * kBucketThreads;
+constexpr int kRangeLevels = 4;                  // curve levels that tell ranges apart
+constexpr int kRangeCells = 1 << (3 * kRangeLevels);
+constexpr int kMaxRanges = 512;                  // per cloud
+constexpr int kSortThreads = 512;
+constexpr int kSortWaves = kSortThreads / kWave;
+constexpr int kSortHeld = 8;                     // points per thread kept in registers
+constexpr int kOneRange = kSortHeld * kSortThreads;   // clouds up to this size: one range
+constexpr int kRangePoints = 1536;               // points per range aimed at above that
+constexpr int kMaxChunks = 1024;                 // per cloud (LDS segment table)
+constexpr int kLogCells = 13;                    // cells per range at most: 32 KB of LDS counters
+constexpr int kLevels = 10;                      // curve levels within a range
+static_assert(static_cast<int64_t>(kMaxChunks) * kSortChunk == kSortMaxPoints, "segment table");
+
+struct P3f {
+    float x, y, z;
+};
+
+// Inclusive prefix sum over the wave in lane order.
+__device__ __forceinline__ uint32_t wave_scan_u32(uint32_t v)
+{
+    const auto step = [](uint32_t x, int moved) { return x + static_cast<uint32_t>(moved); };
+    v = step(v, __builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x111, 0xF, 0xF, false));
+    v = step(v, __builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x112, 0xF, 0xF, false));
+    v = step(v, __builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x114, 0xF, 0xF, false));
+    v = step(v, __builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x118, 0xF, 0xF, false));
+    v = step(v, __builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x142, 0xA, 0xF, false));
+    v = step(v, __builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x143, 0xC, 0xF, false));
+    return v;
+}
+
+// Index along the Hilbert curve of a cell of the 2^kLevels cube (kLevels bits
+// per axis), after Skilling, "Programming the Hilbert curve" (2004): the axes
+// are turned level by level, then Gray-decoded and interleaved.  Neighbours on
+// the curve are neighbours in space, which curve index order is not at its jumps:
+// the searches visit about half as many leaves.
+template <int kLevels>
+__device__ __forceinline__ uint32_t hilbert(uint32_t x, uint32_t y, uint32_t z)
+{
+#pragma unroll
+    for (int l = kLevels - 1; l > 0; --l) {
+        const uint32_t low = (1u << l) - 1u;
+        const auto bit = [&](uint32_t v) { return 0u - ((v >> l) & 1u); };   // all ones if set
+        // Axis bit set: invert x's lower bits; else swap x's and the axis' lower bits.
+        x ^= bit(x) & low;
+        uint32_t t = (x ^ y) & low & ~bit(y);
+        x ^= t ^ (bit(y) & low);
+        y ^= t;
+        t = (x ^ z) & low & ~bit(z);
+        x ^= t ^ (bit(z) & low);
+        z ^= t;
+    }
+    y ^= x;
+    z ^= y;
+    uint32_t t = 0u;
+#pragma unroll
+    for (int l = kLevels - 1; l > 0; --l) t ^= ((1u << l) - 1u) & (0u - ((z >> l) & 1u));
+    x ^= t;
+    y ^= t;
+    z ^= t;
+    uint32_t code = 0u;
+#pragma unroll
+    for (int l = kLevels - 1; l >= 0; --l)
+        code = code << 3 | ((x >> l) & 1u) << 2 | ((y >> l) & 1u) << 1 | ((z >> l) & 1u);
+    return code;
+}
+
+// A box as maxima: -lo, hi.
+struct MaxBox {
+    float v[6];
+    __device__ __forceinline__ void clear()
+    {
+#pragma unroll
+        for (int c = 0; c < 6; ++c) v[c] = -__builtin_inff();
+    }
+    __device__ __forceinline__ void add(float x, float y, float z)
+    {
+        v[0] = fmaxf(v[0], -x);
+        v[1] = fmaxf(v[1], -y);
+        v[2] = fmaxf(v[2], -z);
+        v[3] = fmaxf(v[3], x);
+        v[4] = fmaxf(v[4], y);
+        v[5] = fmaxf(v[5], z);
+    }
+    // Over the workgroup's waves (red: one entry each); ends with a barrier.
+    template <int kWaves>
+    __device__ __forceinline__ void group(float (*red)[6])
+    {
+#pragma unroll
+        for (int c = 0; c < 6; ++c) {
+            v[c] = wave_max(v[c]);
+            if (threadIdx.x % kWave == 0) red[threadIdx.x / kWave][c] = v[c];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c < 6; ++c) v[c] = wave_max(red[threadIdx.x % kWaves][c]);
+    }
+};
+
+}  // namespace
+
+// Curve indices in a box, 2^kLevels cells over its longest side, to any number
+// of levels (fewer levels give the leading bits).  Any value, NaN included,
+// gives an index.
+struct Curve {
+    float lo[3], scale;     // cells per unit at kLevels levels
+    Curve() = default;
+    __device__ __forceinline__ explicit Curve(const MaxBox &b)
+    {
+        lo[0] = -b.v[0];
+        lo[1] = -b.v[1];
+        lo[2] = -b.v[2];
+        const float ext = fmaxf(b.v[3] + b.v[0], fmaxf(b.v[4] + b.v[1], b.v[5] + b.v[2]));
+        scale = ext > 0.0f ? static_cast<float>(1 << kLevels) / ext : 0.0f;
+    }
+    template <int kTo>
+    __device__ __forceinline__ uint32_t code(float x, float y, float z) const
+    {
+        const auto cell = [&](float p, float l) {
+            return static_cast<uint32_t>(__builtin_amdgcn_fmed3f(
+                       (p - l) * scale, 0.0f, static_cast<float>((1 << kLevels) - 1))) >>
+                   (kLevels - kTo);
+        };
+        return hilbert<kTo>(cell(x, lo[0]), cell(y, lo[1]), cell(z, lo[2]));
+    }
+};
+
+namespace {
+
+// Exclusive prefix sums over kPer kWave counters per wave of a workgroup of
+// kWaves waves, in place (all threads; total: one entry per wave); returns the
+// sum of all.  Starts and ends with a barrier.
+template <int kWaves, int kPer>
+__device__ __forceinline__ uint32_t scan_counters(uint32_t *cells, uint32_t *total)
+{
+    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+    uint32_t *mine = cells + wave * kPer * kWave + lane;
+    __syncthreads();
+    uint32_t v[kPer], carry = 0u;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) v[k] = mine[k * kWave];
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        const uint32_t incl = wave_scan_u32(v[k]);
+        v[k] = carry + incl - v[k];
+        carry += __builtin_amdgcn_readlane(incl, kWave - 1);
+    }
+    if (lane == 0) total[wave] = carry;
+    __syncthreads();
+    uint32_t before = 0u, all = 0u;
+#pragma unroll
+    for (int k = 0; k < kWaves; ++k) {
+        const uint32_t t = total[k];
+        before += k < wave ? t : 0u;
+        all += t;
+    }
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) mine[k * kWave] = v[k] + before;
+    __syncthreads();
+    return all;
+}
+
+template <int kWaves>
+__device__ __forceinline__ uint32_t scan_counters(uint32_t *cells, int n, uint32_t *total)
+{
+    constexpr int kGroup = kWaves * kWave;
+    if (n <= kGroup) return scan_counters<kWaves, 1>(cells, total);
+    if (n <= 2 * kGroup) return scan_counters<kWaves, 2>(cells, total);
+    if (n <= 4 * kGroup) return scan_counters<kWaves, 4>(cells, total);
+    if (n <= 8 * kGroup) return scan_counters<kWaves, 8>(cells, total);
+    return scan_counters<kWaves, 16>(cells, total);
+}
+
+// Points of one chunk grouped by range: entries (x, y, z, index) and, per
+// range, the first of its entries (one more offset ends the last range).
+__device__ __forceinline__ void bucket_chunk(const P3f *__restrict__ pts, const SortShape &s,
+                                             int chunk, float4 *__restrict__ entries,
+                                             uint32_t *__restrict__ offs,
+                                             Curve *__restrict__ shared_curve)
+{
+    constexpr int kPerThread = kSortSamples / kBucketThreads;
+    __shared__ uint32_t share[kRangeCells];      // samples per cell, then its range
+    __shared__ uint32_t hist[kMaxRanges];
+    __shared__ float red[kBucketThreads / kWave][6];
+    __shared__ uint32_t total[kBucketThreads / kWave];
+    const int tid = threadIdx.x;
+    const int first = chunk * kSortChunk, last = s.n - 1;
+    P3f p[kBucketHeld], sample[kPerThread];
+#pragma unroll
+    for (int k = 0; k < kPerThread; ++k)
+        sample[k] = pts[static_cast<uint64_t>(k * kBucketThreads + tid) * static_cast<uint32_t>(last) /
+                        (kSortSamples - 1)];
+#pragma unroll
+    for (int k = 0; k < kBucketHeld; ++k) p[k] = pts[min(first + k * kBucketThreads + tid, last)];
+    for (int r = tid; r < kMaxRanges; r += kBucketThreads) hist[r] = 0u;
+    for (int r = tid; r < kRangeCells; r += kBucketThreads) share[r] = 0u;
+    MaxBox box;
+    box.clear();
+#pragma unroll
+    for (int k = 0; k < kPerThread; ++k) box.add(sample[k].x, sample[k].y, sample[k].z);
+    box.group<kBucketThreads / kWave>(red);
+    const Curve curve(box);
+    if (chunk == 0 && tid == 0) *shared_curve = curve;
+#pragma unroll
+    for (int k = 0; k < kPerThread; ++k)
+        atomicAdd(&share[curve.code<kRangeLevels>(sample[k].x, sample[k].y, sample[k].z)], 1u);
+    scan_counters<kBucketThreads / kWave>(share, kRangeCells, total);
+    // A cell whose samples follow t others belongs to range t ranges / samples.
+    // A cell of four ranges' worth of samples or more (many equal points) is
+    // dealt out by index: its points' order says nothing anyway.
+    uint32_t range[kBucketHeld], rank[kBucketHeld];
+#pragma unroll
+    for (int k = 0; k < kBucketHeld; ++k) {
+        const int i = first + k * kBucketThreads + tid;
+        const uint32_t c = curve.code<kRangeLevels>(p[k].x, p[k].y, p[k].z);
+        const uint32_t t = share[c], own = (c + 1 < kRangeCells ? share[c + 1] : kSortSamples) - t;
+        const uint32_t dealt = own * s.ranges >= 4 * kSortSamples
+                                   ? (static_cast<uint32_t>(i) * 2654435761u >> 16) * own >> 16 : 0u;
+        range[k] = min((t + dealt) * s.ranges / kSortSamples, static_cast<uint32_t>(s.ranges) - 1u);
+        if (i <= last) rank[k] = atomicAdd(&hist[range[k]], 1u);
+    }
+    scan_counters<kBucketThreads / kWave>(hist, s.ranges, total);
+    const uint32_t count = static_cast<uint32_t>(min(kSortChunk, s.n - first));
+#pragma unroll
+    for (int k = 0; k < kBucketHeld; ++k) {
+        const int i = first + k * kBucketThreads + tid;
+        if (i <= last)
+            entries[first + hist[range[k]] + rank[k]] =
+                make_float4(p[k].x, p[k].y, p[k].z, __uint_as_float(static_cast<uint32_t>(i)));
+    }
+    uint32_t *o = offs + static_cast<size_t>(chunk) * (s.ranges + 1);
+    for (int r = tid; r < s.ranges; r += kBucketThreads) o[r] = hist[r];
+    if (tid == 0) o[s.ranges] = count;
+}
+
+// Range w of one cloud.
+__device__ __forceinline__ void sort_range(const P3f *__restrict__ pts, const SortShape &s, int w,
+                                           const float4 *__restrict__ entries,
+                                           const uint32_t *__restrict__ offs,
+                                           const Curve *__restrict__ shared_curve,
+                                           float4 *__restrict__ rec, Box *__restrict__ leaf,
+                                           Box *__restrict__ node)
+{
+    __shared__ uint32_t cells[1 << kLogCells];
+    __shared__ uint32_t pre[kMaxChunks + 1], seg[kMaxChunks];
+    __shared__ float red[kSortWaves][6];
+    __shared__ uint32_t total[kSortWaves], below_total[kSortWaves], ends[kSortWaves][2];
+    const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+    const int ncell = 1 << s.log_c, ranges = s.ranges;
+    const bool one = ranges == 1;
+    uint32_t count = static_cast<uint32_t>(s.n), below = 0u;
+    const int scanned = max(ncell, kSortThreads);
+    for (int c = tid; c < scanned; c += kSortThreads) cells[c] = 0u;
+    if (!one) {
+        // The range's segment of every chunk (two chunks per thread), the
+        // points before each, and the points of lower ranges.
+        uint32_t len[2], lower = 0u;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const int c = 2 * tid + k;
+            const uint32_t *o = offs + static_cast<size_t>(min(c, s.chunks - 1)) * (ranges + 1) + w;
+            const uint32_t a = o[0], e = o[1];
+            len[k] = c < s.chunks ? e - a : 0u;
+            lower += c < s.chunks ? a : 0u;
+            if (c < s.chunks) seg[c] = a;
+        }
+        const uint32_t incl = wave_scan_u32(len[0] + len[1]), li = wave_scan_u32(lower);
+        if (lane == kWave - 1) {
+            total[wave] = incl;
+            below_total[wave] = li;
+        }
+        __syncthreads();
+        uint32_t before = incl - len[0] - len[1];
+        count = 0u;
+#pragma unroll
+        for (int k = 0; k < kSortWaves; ++k) {
+            const uint32_t t = total[k];
+            before += k < wave ? t : 0u;
+            count += t;
+            below += below_total[k];
+        }
+        if (2 * tid < s.chunks) pre[2 * tid] = before;
+        if (2 * tid + 1 < s.chunks) pre[2 * tid + 1] = before + len[0];
+        if (tid == 0) pre[s.chunks] = count;
+        __syncthreads();
+    }
+    // Point i of the range.
+    const auto fetch = [&](uint32_t i) -> float4 {
+        if (one) {
+            const P3f p = pts[i];
+            return make_float4(p.x, p.y, p.z, __uint_as_float(i));
+        }
+        int lo = 0, hi = s.chunks;
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (pre[mid] <= i) lo = mid; else hi = mid;
+        }
+        return entries[static_cast<uint32_t>(lo) * kSortChunk + seg[lo] + (i - pre[lo])];
+    };
+    const uint32_t start = (below + kNode - 1) / kNode * kNode + static_cast<uint32_t>(w) * kNode;
+    const uint32_t next = (below + count + kNode - 1) / kNode * kNode + static_cast<uint32_t>(w + 1) * kNode;
+    float4 *out = rec + start;
+    if (count > 0u) {
+        const bool held = count <= kSortHeld * kSortThreads;
+        float4 p[kSortHeld];
+        Curve curve;
+        if (held) {
+#pragma unroll
+            for (int k = 0; k < kSortHeld; ++k)
+                if (static_cast<uint32_t>(k * kSortThreads) < count)
+                    p[k] = fetch(min(static_cast<uint32_t>(k * kSortThreads + tid), count - 1));
+                else
+                    p[k] = p[0];
+        }
+        if (one) {
+            MaxBox box;
+            box.clear();
+            if (held) {
+#pragma unroll
+                for (int k = 0; k < kSortHeld; ++k) box.add(p[k].x, p[k].y, p[k].z);
+            } else {
+                for (uint32_t i = tid; i < count; i += kSortThreads) {
+                    const float4 q = fetch(i);
+                    box.add(q.x, q.y, q.z);
+                }
+            }
+            box.group<kSortWaves>(red);
+            curve = Curve(box);
+        } else {
+            curve = *shared_curve;
+        }
+        // The range's codes from the lowest on, in as many cells as there are.
+        uint32_t code[kSortHeld], rank[kSortHeld], low = kNoPoint, high = 0u;
+        if (held) {
+#pragma unroll
+            for (int k = 0; k < kSortHeld; ++k) {
+                if (static_cast<uint32_t>(k * kSortThreads) >= count) continue;
+                code[k] = curve.code<kLevels>(p[k].x, p[k].y, p[k].z);
+                low = min(low, code[k]);
+                high = max(high, code[k]);
+            }
+        } else {
+            for (uint32_t i = tid; i < count; i += kSortThreads) {
+                const float4 q = fetch(i);
+                const uint32_t c = curve.code<kLevels>(q.x, q.y, q.z);
+                low = min(low, c);
+                high = max(high, c);
+            }
+        }
+        low = wave_min_u32(low);
+        high = ~wave_min_u32(~high);
+        if (lane == 0) {
+            ends[wave][0] = low;
+            ends[wave][1] = ~high;
+        }
+        __syncthreads();
+        low = wave_min_u32(ends[lane % kSortWaves][0]);
+        high = ~wave_min_u32(ends[lane % kSortWaves][1]);
+        const int down = max(32 - __builtin_clz((high - low) | 1u) - s.log_c, 0);
+        if (held) {
+#pragma unroll
+            for (int k = 0; k < kSortHeld; ++k)
+                if (static_cast<uint32_t>(k * kSortThreads + tid) < count)
+                    rank[k] = atomicAdd(&cells[(code[k] - low) >> down], 1u);
+        } else {
+            for (uint32_t i = tid; i < count; i += kSortThreads) {
+                const float4 q = fetch(i);
+                atomicAdd(&cells[(curve.code<kLevels>(q.x, q.y, q.z) - low) >> down], 1u);
+            }
+        }
+        scan_counters<kSortWaves>(cells, scanned, total);
+        if (held) {
+#pragma unroll
+            for (int k = 0; k < kSortHeld; ++k)
+                if (static_cast<uint32_t>(k * kSortThreads + tid) < count) out[cells[(code[k] - low) >> down] + rank[k]] = p[k];
+        } else {
+            for (uint32_t i = tid; i < count; i += kSortThreads) {
+                const float4 q = fetch(i);
+                out[atomicAdd(&cells[(curve.code<kLevels>(q.x, q.y, q.z) - low) >> down], 1u)] = q;
+            }
+        }
+        const uint32_t filled = (count + kTile - 1) / kTile * kTile;
+        for (uint32_t t = count + tid; t < filled; t += kSortThreads)
+            out[t] = make_float4(kFarAway, 0.0f, 0.0f, __uint_as_float(kNoPoint));
+        __syncthreads();
+    }
+    // Boxes: a wave takes a node, a lane a leaf.
+    for (uint32_t nd = start / kNode + wave; nd < next / kNode; nd += kSortWaves) {
+        const uint32_t r0 = nd * kNode + lane * kLeaf - start;   // first record of the leaf
+        MaxBox b;
+        b.clear();
+        uint32_t first = kNoPoint;
+        if (r0 < count) {
+            const uint32_t m = min(static_cast<uint32_t>(kLeaf), count - r0);
+            const float4 *src = out + r0;
+#pragma unroll
+            for (uint32_t u = 0; u < kLeaf; ++u) {
+                const float4 q = src[min(u, m - 1)];
+                b.add(q.x, q.y, q.z);
+                first = min(first, __float_as_uint(q.w));
+            }
+        }
+        leaf[static_cast<size_t>(nd) * kNodeLeaves + lane] =
+            Box{-b.v[0], -b.v[1], -b.v[2], first, b.v[3], b.v[4], b.v[5], 0u};
+#pragma unroll
+        for (int c = 0; c < 6; ++c) b.v[c] = wave_max(b.v[c]);
+        first = wave_min_u32(first);
+        if (lane == 0) node[nd] = Box{-b.v[0], -b.v[1], -b.v[2], first, b.v[3], b.v[4], b.v[5], 0u};
+    }
+}
+
+struct SortArgs {
+    SortJob job[2];
+    uint32_t *counter;
+};
+
+__global__ __launch_bounds__(kBucketThreads) void bucket_kernel(SortArgs a)
+{
+    const uint32_t wg = xcd_block();
+    const uint32_t c0 = a.job[0].s.chunks, c1 = a.job[1].s.chunks;
+    const int64_t b = wg / (c0 + c1);
+    const uint32_t c = wg % (c0 + c1);
+    const SortJob &t = a.job[c < c0 ? 0 : 1];
+    if (t.s.ranges == 1) return;     // sorted straight from the cloud
+    bucket_chunk(reinterpret_cast<const P3f *>(t.P) + b * t.s.n, t.s,
+                 static_cast<int>(c < c0 ? c : c - c0),
+                 t.entries + b * t.s.chunks * kSortChunk,
+                 t.offs + b * t.s.chunks * (t.s.ranges + 1), t.curve + b);
+}
+
+__global__ __launch_bounds__(kSortThreads) void sort_kernel(SortArgs a)
+{
+    if (blockIdx.x == 0 && threadIdx.x == 0) *a.counter = 0u;
+    const uint32_t wg = xcd_block();
+    const uint32_t w0 = a.job[0].s.ranges, w1 = a.job[1].s.ranges;
+    const int64_t b = wg / (w0 + w1);
+    const uint32_t w = wg % (w0 + w1);
+    const SortJob &t = a.job[w < w0 ? 0 : 1];
+    sort_range(reinterpret_cast<const P3f *>(t.P) + b * t.s.n, t.s,
+               static_cast<int>(w < w0 ? w : w - w0), t.entries + b * t.s.chunks * kSortChunk,
+               t.offs + b * t.s.chunks * (t.s.ranges + 1), t.curve + b,
+               t.rec + b * t.s.nodes * kNode, t.leaf + b * t.s.nodes * kNodeLeaves,
+               t.node + b * t.s.nodes);
+}
+
+int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
+
+size_t align256(size_t x) { return (x + 255) & ~static_cast<size_t>(255); }
+
+int ceil_log2(int64_t x)
+{
+    int l = 0;
+    while ((int64_t{1} << l) < x) ++l;
+    return l;
+}
+
+}  // namespace
+
+SortPlan plan_sort(int64_t B, int64_t n, size_t &at)
+{
+    SortPlan p{};
+    p.B = B;
+    p.s.n = static_cast<int32_t>(n);
+    p.s.chunks = static_cast<int32_t>(ceil_div(n, kSortChunk));
+    p.s.ranges = n <= kOneRange ? 1 : static_cast<int32_t>(std::min<int64_t>(ceil_div(n, kRangePoints), kMaxRanges));
+    p.s.log_c = std::min(std::max(ceil_log2(n) + 2, 9), kLogCells);
+    p.s.nodes = static_cast<int32_t>(ceil_div(n, kNode) + p.s.ranges);
+    const size_t b = static_cast<size_t>(B);
+    const auto place = [&](size_t &where, size_t bytes) {
+        where = at;
+        at += align256(bytes);
+    };
+    place(p.entries, p.s.ranges > 1 ? b * p.s.chunks * kSortChunk * sizeof(float4) : 0);
+    place(p.offs, p.s.ranges > 1 ? b * p.s.chunks * (p.s.ranges + 1) * 4 : 0);
+    place(p.curve, b * sizeof(Curve));
+    place(p.rec, b * p.s.nodes * kNode * sizeof(float4));
+    place(p.leaf, b * p.s.nodes * kNodeLeaves * sizeof(Box));
+    place(p.node, b * p.s.nodes * sizeof(Box));
+    return p;
+}
+
+SortJob sort_job(const SortPlan &p, const float *P, char *ws)
+{
+    SortJob j{};
+    j.P = P;
+    j.rec = reinterpret_cast<float4 *>(ws + p.rec);
+    j.leaf = reinterpret_cast<Box *>(ws + p.leaf);
+    j.node = reinterpret_cast<Box *>(ws + p.node);
+    j.entries = reinterpret_cast<float4 *>(ws + p.entries);
+    j.offs = reinterpret_cast<uint32_t *>(ws + p.offs);
+    j.curve = reinterpret_cast<Curve *>(ws + p.curve);
+    j.s = p.s;
+    return j;
+}
+
+hipError_t launch_sort(int64_t B, const SortJob &a, const SortJob &b, uint32_t *counter,
+                       hipStream_t stream)
+{
+    const SortArgs args{{a, b}, counter};
+    if (a.s.ranges > 1 || b.s.ranges > 1)
+        bucket_kernel<<<static_cast<uint32_t>(B * (static_cast<int64_t>(a.s.chunks) + b.s.chunks)),
+                        kBucketThreads, 0, stream>>>(args);
+    sort_kernel<<<static_cast<uint32_t>(B * (static_cast<int64_t>(a.s.ranges) + b.s.ranges)),
+                  kSortThreads, 0, stream>>>(args);
+    return hipGetLastError();
+}
+
+}  // namespace cdk

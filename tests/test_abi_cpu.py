@@ -446,3 +446,18 @@ def test_best_forward_workspace(lib):
         assert best >= need and best % 256 == 0 and (best == need or best <= 4 << 30)
     for B, N, M in ((0, 10, 10), (1, 0, 10), (-1, 10, 10), (2, 2 ** 30, 2 ** 30)):
         assert lib.cd_workspace_bytes_best(B, N, M) == 0
+
+
+def test_best_p2s_workspace(lib):
+    # What cd_p2s_workspace_bytes needs or more, more only from 1.5e8 pairs,
+    # 1024 points and 2048 faces on; 0 where that is 0.
+    lib.cd_p2s_workspace_bytes_best.restype = ctypes.c_size_t
+    lib.cd_p2s_workspace_bytes_best.argtypes = [ctypes.c_int64] * 4
+    for B, S, nv, nf in ((16, 16384, 2562, 5120), (4, 1000, 100, 320), (1, 74000, 1000, 2047),
+                         (64, 1023, 1000, 4000), (1, 2 ** 22, 1000, 4000), (2, 0, 30, 10),
+                         (1, 73243, 1156, 2178), (2, -1, 30, 10), (2, 5, 30, 0)):
+        need = lib.cd_p2s_workspace_bytes(B, S, nv, nf)
+        best = lib.cd_p2s_workspace_bytes_best(B, S, nv, nf)
+        assert best >= need and best % 256 == 0 and (best == 0) == (need == 0)
+        pruned = B * S * nf >= 1.5e8 and 2 ** 21 >= S >= 1024 and nf >= 2048
+        assert (best > need) == pruned, (B, S, nv, nf)
