@@ -9,17 +9,24 @@
 // sum_ij P_ij C_ij; its backward holds P fixed:
 //     d cost / d x_i = sum_j P_ij (x_i - y_j) / C_ij,  d cost / d y_j = the opposite sum.
 //
-//  * lse_kernel: one half-update.  A workgroup holds 1024 queries (4 per
-//    lane) in VGPRs and walks a block of targets; the target index is
-//    wave-uniform, so coordinates and potentials arrive by scalar loads.  The
-//    log-sum-exp runs in base 2 online over batches of 16 targets: the batch
-//    maximum rescales the running sum once per batch, then each pair adds
-//    exp2(z - max), z = (g_j - C_ij) log2(e) / eps.  With several target
-//    blocks a half-update leaves (max, sum) partials per query; the next
-//    half-update merges them for its own target block (1024 targets at a time
-//    into LDS) instead of reading finished potentials, and lse_merge_kernel
-//    merges them, with the same function, only where finished potentials are
-//    needed (the outputs).
+//  * lse_kernel: one half-update.  A workgroup of 16 waves holds 64, 128 or 256
+//    queries (1, 2 or 4 per lane, the same in every wave) in VGPRs; each wave
+//    walks a sixteenth of the targets, whose index is wave-uniform, so that
+//    coordinates and scaled potential (one float4, written by the half-update
+//    before) arrive by scalar loads.  The log-sum-exp runs in base 2 online over
+//    batches of targets: the batch maximum rescales the running sum once, then
+//    each pair adds exp2(z - max), z = (g_j - C_ij) log2(e) / eps.  The waves'
+//    (max, sum) meet in LDS and the finished potentials are written, so that a
+//    half-update is one launch and leaves no partials: with the targets split
+//    over workgroups, the next half-update merged the partials of its targets
+//    again in every query group (57.0 us a half-update of 32 x 2048^2 against 54.0,
+//    13.5 against 6.5 on 2 x 500 x 701, 826 against 598 us for 20 iterations of
+//    4 x 300 x 3000).  Queries per lane: as many as leave one workgroup per CU.
+//    Bound by instruction issue: 12 instructions a term, two of them
+//    transcendental at about 9 cycles each, 62 cycles per 64 terms.  Measured and
+//    not kept: targets through LDS (6315 against 5420 us for the 50 iterations
+//    of 32 x 2048^2), scalar loads a batch ahead (5693: the compiler moves them to
+//    VGPRs), 8 waves (5623), 8 or fewer targets a batch with fewer queries.
 //  * plan_kernel: per (query block, target block) tile, either the tile's
 //    sum of P_ij C_ij (in double, reduced in a fixed order) or per query
 //    the sum of P_ij (q_i - t_j) / C_ij; partial sums over target blocks are
@@ -38,41 +45,27 @@ namespace {
 constexpr int kEQ = 4;                      // queries per lane
 constexpr int kEThreads = 256;              // 4 waves
 constexpr int kEGroup = kEQ * kEThreads;    // queries per workgroup
-constexpr int kEBatch = 16;                 // targets per online-LSE batch
+constexpr int kEBatch = 16;                 // targets per batch of a plan pass
 constexpr int kEMinTB = 64;                 // targets per block, at least
 constexpr int64_t kETargetTiles = 512;
-constexpr int kEChunk = 1024;               // target potentials merged into LDS at a time
+constexpr int kLseWaves = 16;               // waves of a half-update's workgroup
+constexpr int kLseStep = 16;                // targets per wave: a multiple
+constexpr int64_t kCUs = 256;
 constexpr int kThreads = 256;
 constexpr float kLog2e = 1.4426950408889634f;
 
 struct LseArgs {
-    const float *Q, *T;     // [B, nq, 3], [B, nt, 3]
-    const float *pt;        // [B, nt] potentials of the targets (finished)
-    const float2 *tpart;    // or their partials [B, tnTB, nt] from the previous half-update
+    const float *Q;         // [B, nq, 3]
+    const float4 *T;        // [B, nt] targets: coordinates, potential times k
+    float4 *Q4;             // [B, nq] the queries as targets of the next half-update
     float *pq;              // [B, nq] updated potentials of the queries
-    float2 *part;           // [B, nTB, nq] (max, sum) partials, base 2
     int64_t nq, nt;
     float k;                // log2(e) / eps
+    float k_next;           // that of the next half-update
     float out_scale;        // -eps ln 2
     float out_bias;         // eps log(nt)  (= -eps log b)
-    float t_scale, t_bias;  // out_scale, out_bias of the half-update that left tpart
-    int nQG, nTB, TB, tnTB;
+    int nQG, per;           // query groups per item; targets per wave
 };
-
-// A finished potential from its nTB (max, sum) partials, stride apart:
-// -eps log(b sum exp(...)) = scale (M + log2 S) + bias.
-__device__ __forceinline__ float merged_potential(const float2 *p, int nTB, int64_t stride,
-                                                  float scale, float bias)
-{
-    float M = -__builtin_inff();
-    for (int t = 0; t < nTB; ++t) M = __builtin_fmaxf(M, p[static_cast<int64_t>(t) * stride].x);
-    float S = 0.0f;
-    for (int t = 0; t < nTB; ++t) {
-        const float2 v = p[static_cast<int64_t>(t) * stride];
-        S += v.y * __builtin_amdgcn_exp2f(v.x - M);
-    }
-    return __builtin_fmaf(scale, M + __log2f(S), bias);
-}
 
 __device__ __forceinline__ float dist2(float qx, float qy, float qz, float tx, float ty, float tz)
 {
@@ -80,47 +73,42 @@ __device__ __forceinline__ float dist2(float qx, float qy, float qz, float tx, f
     return __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dx * dx));
 }
 
-// One batch of kEBatch targets for kEQ queries: running max m and sum s.
-__device__ __forceinline__ void lse_batch(const float (&qx)[kEQ], const float (&qy)[kEQ],
-                                          const float (&qz)[kEQ], float (&m)[kEQ],
-                                          float (&s)[kEQ], const float (&tx)[kEBatch],
-                                          const float (&ty)[kEBatch], const float (&tz)[kEBatch],
-                                          const float (&tk)[kEBatch], float kk)
+// One batch of kB targets for kQ queries: running max m and sum s.
+template <int kQ, int kB>
+__device__ __forceinline__ void lse_batch(const float (&qx)[kQ], const float (&qy)[kQ],
+                                          const float (&qz)[kQ], float (&m)[kQ], float (&s)[kQ],
+                                          const float4 (&t)[kB], float kk)
 {
 #pragma unroll
-    for (int k = 0; k < kEQ; ++k) {
-        float z[kEBatch];
+    for (int k = 0; k < kQ; ++k) {
+        float z[kB];
         float bm = -__builtin_inff();
 #pragma unroll
-        for (int u = 0; u < kEBatch; ++u) {
-            const float c = __builtin_amdgcn_sqrtf(dist2(qx[k], qy[k], qz[k], tx[u], ty[u], tz[u]));
-            z[u] = __builtin_fmaf(-c, kk, tk[u]);
+        for (int u = 0; u < kB; ++u) {
+            const float c = __builtin_amdgcn_sqrtf(dist2(qx[k], qy[k], qz[k], t[u].x, t[u].y, t[u].z));
+            z[u] = __builtin_fmaf(-c, kk, t[u].w);
             bm = __builtin_fmaxf(bm, z[u]);
         }
         const float mn = __builtin_fmaxf(m[k], bm);
         float acc = s[k] * __builtin_amdgcn_exp2f(m[k] - mn);
 #pragma unroll
-        for (int u = 0; u < kEBatch; ++u) acc += __builtin_amdgcn_exp2f(z[u] - mn);
+        for (int u = 0; u < kB; ++u) acc += __builtin_amdgcn_exp2f(z[u] - mn);
         s[k] = acc;
         m[k] = mn;
     }
 }
 
-// kFromParts: the targets' potentials come as the previous half-update's
-// partials, merged here a chunk at a time into LDS.
-template <bool kFromParts>
-__global__ __launch_bounds__(kEThreads) void lse_kernel(LseArgs a)
+template <int kQ, int kB>
+__global__ __launch_bounds__(kLseWaves * kWave) void lse_kernel(LseArgs a)
 {
-    __shared__ float lpt[kFromParts ? kEChunk : 1];
-    const int64_t per_item = static_cast<int64_t>(a.nQG) * a.nTB;
-    const int64_t b = blockIdx.x / per_item;
-    const int rest = static_cast<int>(blockIdx.x % per_item);
-    const int qg = rest / a.nTB, tb = rest % a.nTB;
-    const int64_t q0 = static_cast<int64_t>(qg) * kEGroup;
-    float qx[kEQ], qy[kEQ], qz[kEQ], m[kEQ], s[kEQ];
+    __shared__ float2 part[kLseWaves][kQ * kWave];
+    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+    const int64_t b = blockIdx.x / a.nQG;
+    const int64_t q0 = static_cast<int64_t>(blockIdx.x % a.nQG) * (kQ * kWave);
+    float qx[kQ], qy[kQ], qz[kQ], m[kQ], s[kQ];
 #pragma unroll
-    for (int k = 0; k < kEQ; ++k) {
-        const int64_t q = std::min<int64_t>(q0 + k * kEThreads + threadIdx.x, a.nq - 1);
+    for (int k = 0; k < kQ; ++k) {
+        const int64_t q = std::min<int64_t>(q0 + k * kWave + lane, a.nq - 1);
         const float *p = a.Q + (b * a.nq + q) * 3;
         qx[k] = p[0];
         qy[k] = p[1];
@@ -128,75 +116,62 @@ __global__ __launch_bounds__(kEThreads) void lse_kernel(LseArgs a)
         m[k] = -__builtin_inff();
         s[k] = 0.0f;
     }
-    // Targets [j0, j1) of item b; 32-bit offsets within the item.
-    const int j0 = tb * a.TB;
-    const int j1 = static_cast<int>(std::min<int64_t>(static_cast<int64_t>(j0) + a.TB, a.nt));
-    const float *Tb = a.T + b * a.nt * 3;
-    const float *pb = kFromParts ? nullptr : a.pt + b * a.nt;
+    // This wave's targets; the index is the same for all its lanes, so that
+    // they arrive by scalar loads.
+    const float4 *Tb = a.T + b * a.nt;
     const float kk = a.k;
-    // Chunks of kEChunk targets (a multiple of kEBatch, so only the last
-    // chunk has a tail); without partials the whole block is one chunk.
-    for (int c0 = j0; c0 < j1; c0 += (kFromParts ? kEChunk : j1 - j0)) {
-        const int c1 = kFromParts ? std::min(c0 + kEChunk, j1) : j1;
-        if (kFromParts) {
-            __syncthreads();  // the previous chunk is consumed
-            const float2 *tp = a.tpart + b * a.tnTB * a.nt;
-            for (int j = c0 + static_cast<int>(threadIdx.x); j < c1; j += kEThreads)
-                lpt[j - c0] = merged_potential(tp + j, a.tnTB, a.nt, a.t_scale, a.t_bias);
-            __syncthreads();
-        }
-        auto pot = [&](int j) { return kFromParts ? lpt[j - c0] : pb[j]; };
-        const int cfull = c0 + (c1 - c0) / kEBatch * kEBatch;
-        for (int jb = c0; jb < cfull; jb += kEBatch) {
-            // A full batch: contiguous wave-uniform loads, no per-target guards.
-            float tx[kEBatch], ty[kEBatch], tz[kEBatch], tk[kEBatch];
+    const int nt = static_cast<int>(a.nt);
+    int j = __builtin_amdgcn_readfirstlane(
+        static_cast<int>(std::min<int64_t>(static_cast<int64_t>(wave) * a.per, nt)));
+    const int j1 = static_cast<int>(std::min<int64_t>(static_cast<int64_t>(j) + a.per, nt));
+    for (; j + kB <= j1; j += kB) {
+        float4 t[kB];
 #pragma unroll
-            for (int u = 0; u < kEBatch; ++u) {
-                tx[u] = Tb[3 * (jb + u) + 0];
-                ty[u] = Tb[3 * (jb + u) + 1];
-                tz[u] = Tb[3 * (jb + u) + 2];
-                tk[u] = pot(jb + u) * kk;
-            }
-            lse_batch(qx, qy, qz, m, s, tx, ty, tz, tk, kk);
-        }
-        if (cfull < c1) {
-            // The tail: clamped loads, weight 0 past the end.
-            float tx[kEBatch], ty[kEBatch], tz[kEBatch], tk[kEBatch];
+        for (int u = 0; u < kB; ++u) t[u] = Tb[j + u];
+        lse_batch<kQ, kB>(qx, qy, qz, m, s, t, kk);
+    }
+    if (j < j1) {
+        // The tail: clamped loads, weight 0 past the end.
+        float4 t[kB];
 #pragma unroll
-            for (int u = 0; u < kEBatch; ++u) {
-                const int j = std::min(cfull + u, c1 - 1);
-                tx[u] = Tb[3 * j + 0];
-                ty[u] = Tb[3 * j + 1];
-                tz[u] = Tb[3 * j + 2];
-                tk[u] = cfull + u < c1 ? pot(j) * kk : -__builtin_inff();
-            }
-            lse_batch(qx, qy, qz, m, s, tx, ty, tz, tk, kk);
+        for (int u = 0; u < kB; ++u) {
+            t[u] = Tb[std::min(j + u, j1 - 1)];
+            t[u].w = j + u < j1 ? t[u].w : -__builtin_inff();
         }
+        lse_batch<kQ, kB>(qx, qy, qz, m, s, t, kk);
     }
 #pragma unroll
-    for (int k = 0; k < kEQ; ++k) {
-        const int64_t q = q0 + k * kEThreads + threadIdx.x;
-        if (q >= a.nq) continue;
-        if (a.nTB == 1)
-            a.pq[b * a.nq + q] = __builtin_fmaf(a.out_scale, m[k] + __log2f(s[k]), a.out_bias);
-        else
-            a.part[(b * a.nTB + tb) * a.nq + q] = make_float2(m[k], s[k]);
+    for (int k = 0; k < kQ; ++k) part[wave][k * kWave + lane] = make_float2(m[k], s[k]);
+    __syncthreads();
+    // A thread merges one query's (max, sum) of all waves, in order:
+    // -eps log(b sum exp(...)) = scale (M + log2 S) + bias.
+    const int64_t q = q0 + threadIdx.x;
+    if (threadIdx.x >= kQ * kWave || q >= a.nq) return;
+    float2 v[kLseWaves];
+    float M = -__builtin_inff(), S = 0.0f;
+#pragma unroll
+    for (int w = 0; w < kLseWaves; ++w) {
+        v[w] = part[w][threadIdx.x];
+        M = __builtin_fmaxf(M, v[w].x);
     }
+#pragma unroll
+    for (int w = 0; w < kLseWaves; ++w) S += v[w].y * __builtin_amdgcn_exp2f(v[w].x - M);
+    const float pot = __builtin_fmaf(a.out_scale, M + __log2f(S), a.out_bias);
+    a.pq[b * a.nq + q] = pot;
+    a.Q4[b * a.nq + q].w = pot * a.k_next;
 }
 
-__global__ __launch_bounds__(kThreads) void lse_merge_kernel(LseArgs a, int64_t B)
+// Both clouds as targets; the y's with their starting potential g (nullptr: 0).
+__global__ __launch_bounds__(kThreads) void targets_kernel(int64_t nx, int64_t ny, const float *X,
+                                                           const float *Y, const float *g, float k,
+                                                           float4 *X4, float4 *Y4)
 {
-    const int64_t k = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
-    if (k >= B * a.nq) return;
-    const int64_t b = k / a.nq, q = k - b * a.nq;
-    a.pq[k] = merged_potential(a.part + b * a.nTB * a.nq + q, a.nTB, a.nq, a.out_scale,
-                               a.out_bias);
-}
-
-__global__ __launch_bounds__(kThreads) void fill_kernel(float *p, int64_t n, float v)
-{
-    const int64_t k = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
-    if (k < n) p[k] = v;
+    int64_t i = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
+    if (i >= nx + ny) return;
+    const bool y = i >= nx;
+    i -= y ? nx : 0;
+    const float *p = (y ? Y : X) + 3 * i;
+    (y ? Y4 : X4)[i] = make_float4(p[0], p[1], p[2], y && g ? g[i] * k : 0.0f);
 }
 
 struct PlanArgs {
@@ -372,9 +347,8 @@ Tiles tiles_for(int64_t B, int64_t nq, int64_t nt)
 }
 
 struct EmdLayout {
-    Tiles xy, yx;               // queries X against Y; queries Y against X
-    size_t fpart_bytes;         // f's partials; g's follow (a half-update reads one, writes the other)
-    size_t part_bytes, cost_bytes, grad_bytes;
+    Tiles xy, yx;               // plan passes: queries X against Y; queries Y against X
+    size_t x4_bytes, y4_bytes, cost_bytes, grad_bytes;
 };
 
 EmdLayout layout(int64_t B, int64_t N, int64_t M)
@@ -382,10 +356,8 @@ EmdLayout layout(int64_t B, int64_t N, int64_t M)
     EmdLayout L;
     L.xy = tiles_for(B, N, M);
     L.yx = tiles_for(B, M, N);
-    const size_t p1 = L.xy.nTB > 1 ? static_cast<size_t>(B * L.xy.nTB * N) * 8 : 0;
-    const size_t p2 = L.yx.nTB > 1 ? static_cast<size_t>(B * L.yx.nTB * M) * 8 : 0;
-    L.fpart_bytes = align256(p1);
-    L.part_bytes = L.fpart_bytes + align256(p2);
+    L.x4_bytes = align256(static_cast<size_t>(B * N) * sizeof(float4));
+    L.y4_bytes = align256(static_cast<size_t>(B * M) * sizeof(float4));
     L.cost_bytes = align256(static_cast<size_t>(B * L.xy.nQG * L.xy.nTB) * 8);
     const size_t g1 = L.xy.nTB > 1 ? static_cast<size_t>(B * L.xy.nTB * N) * 12 : 0;
     const size_t g2 = L.yx.nTB > 1 ? static_cast<size_t>(B * L.yx.nTB * M) * 12 : 0;
@@ -393,69 +365,32 @@ EmdLayout layout(int64_t B, int64_t N, int64_t M)
     return L;
 }
 
-// The potentials of one cloud between half-updates: finished values, or the
-// (max, sum) partials a half-update left with the transform that finishes them.
-struct Potentials {
-    const float *fin = nullptr;     // [B, n], or
-    const float2 *part = nullptr;   // [B, nTB, n]
-    int nTB = 1;
-    float scale = 0.0f, bias = 0.0f;
-};
-
-// One half-update of the queries' potentials (written to pq when the targets
-// form one block, else left as partials in `part`) against the targets'.
-Potentials lse_pass(int64_t B, const float *Q, int64_t nq, const float *T, int64_t nt,
-                    const Potentials &tp, float *pq, float eps, const Tiles &t, float2 *part,
-                    hipStream_t stream)
+// One half-update of the queries' potentials.
+void lse_pass(int64_t B, const float *Q, float4 *Q4, int64_t nq, const float4 *T, int64_t nt,
+              float *pq, float eps, float eps_next, hipStream_t stream)
 {
     LseArgs a{};
     a.Q = Q;
     a.T = T;
-    a.pt = tp.fin;
-    a.tpart = tp.part;
-    a.tnTB = tp.nTB;
-    a.t_scale = tp.scale;
-    a.t_bias = tp.bias;
+    a.Q4 = Q4;
     a.pq = pq;
-    a.part = part;
     a.nq = nq;
     a.nt = nt;
     a.k = kLog2e / eps;
+    a.k_next = kLog2e / eps_next;
     a.out_scale = -eps * 0.6931471805599453f;
     a.out_bias = static_cast<float>(static_cast<double>(eps) * std::log(static_cast<double>(nt)));
-    a.nQG = t.nQG;
-    a.nTB = t.nTB;
-    a.TB = t.TB;
-    const uint32_t grid = static_cast<uint32_t>(B * t.nQG * t.nTB);
-    if (tp.fin)
-        lse_kernel<false><<<grid, kEThreads, 0, stream>>>(a);
+    a.per = static_cast<int>(ceil_div(ceil_div(nt, kLseWaves), kLseStep) * kLseStep);
+    const auto groups = [&](int q) { return B * ceil_div(nq, q * kWave); };
+    const int q = groups(4) >= kCUs ? 4 : groups(2) >= kCUs ? 2 : 1;
+    a.nQG = static_cast<int>(ceil_div(nq, q * kWave));
+    const uint32_t grid = static_cast<uint32_t>(groups(q));
+    if (q == 4)
+        lse_kernel<4, 8><<<grid, kLseWaves * kWave, 0, stream>>>(a);
+    else if (q == 2)
+        lse_kernel<2, 16><<<grid, kLseWaves * kWave, 0, stream>>>(a);
     else
-        lse_kernel<true><<<grid, kEThreads, 0, stream>>>(a);
-    Potentials out;
-    if (t.nTB == 1) {
-        out.fin = pq;
-    } else {
-        out.part = part;
-        out.nTB = t.nTB;
-        out.scale = a.out_scale;
-        out.bias = a.out_bias;
-    }
-    return out;
-}
-
-// Finished potentials [B, n] into `out` (a no-op if they are there already).
-void finish(int64_t B, int64_t n, const Potentials &p, float *out, hipStream_t stream)
-{
-    if (p.fin) return;
-    LseArgs a{};
-    a.part = const_cast<float2 *>(p.part);
-    a.pq = out;
-    a.nq = n;
-    a.nTB = p.nTB;
-    a.out_scale = p.scale;
-    a.out_bias = p.bias;
-    lse_merge_kernel<<<static_cast<uint32_t>(ceil_div(B * n, kThreads)), kThreads, 0, stream>>>(
-        a, B);
+        lse_kernel<1, 16><<<grid, kLseWaves * kWave, 0, stream>>>(a);
 }
 
 hipError_t plan_pass(int64_t B, const float *Q, int64_t nq, const float *T, int64_t nt,
@@ -495,7 +430,7 @@ hipError_t plan_pass(int64_t B, const float *Q, int64_t nq, const float *T, int6
 size_t emd_workspace_bytes(int64_t B, int64_t N, int64_t M)
 {
     const EmdLayout L = layout(B, N, M);
-    return L.part_bytes + L.cost_bytes + L.grad_bytes;
+    return L.x4_bytes + L.y4_bytes + L.cost_bytes + L.grad_bytes;
 }
 
 float emd_eps(double eps_start, double eps_end, int n_iters, int t)
@@ -512,26 +447,20 @@ hipError_t launch_emd_forward(int64_t B, int64_t N, int64_t M, const float *X, c
 {
     const EmdLayout L = layout(B, N, M);
     char *base = static_cast<char *>(ws);
-    float2 *fpart = reinterpret_cast<float2 *>(base);
-    float2 *gpart = reinterpret_cast<float2 *>(base + L.fpart_bytes);
-    double *cost_part = reinterpret_cast<double *>(base + L.part_bytes);
-    if (!warm)
-        fill_kernel<<<static_cast<uint32_t>(ceil_div(B * M, kThreads)), kThreads, 0, stream>>>(
-            g, B * M, 0.0f);
-    Potentials pf, pg;
-    pf.fin = f;
-    pg.fin = g;
+    float4 *X4 = reinterpret_cast<float4 *>(base);
+    float4 *Y4 = reinterpret_cast<float4 *>(base + L.x4_bytes);
+    double *cost_part = reinterpret_cast<double *>(base + L.x4_bytes + L.y4_bytes);
+    targets_kernel<<<static_cast<uint32_t>(ceil_div(B * (N + M), kThreads)), kThreads, 0, stream>>>(
+        B * N, B * M, X, Y, warm ? g : nullptr, kLog2e / emd_eps(eps_start, eps_end, n_iters, 0), X4, Y4);
+    hipError_t e;
     for (int t = 0; t < n_iters; ++t) {
         const float eps = emd_eps(eps_start, eps_end, n_iters, t);
-        pf = lse_pass(B, X, N, Y, M, pg, f, eps, L.xy, fpart, stream);
-        pg = lse_pass(B, Y, M, X, N, pf, g, eps, L.yx, gpart, stream);
-        const hipError_t e = hipGetLastError();
+        const float next = emd_eps(eps_start, eps_end, n_iters, std::min(t + 1, n_iters - 1));
+        lse_pass(B, X, X4, N, Y4, M, f, eps, eps, stream);
+        lse_pass(B, Y, Y4, M, X4, N, g, eps, next, stream);
+        e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    finish(B, N, pf, f, stream);
-    finish(B, M, pg, g, stream);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
     const float eps = emd_eps(eps_start, eps_end, n_iters, n_iters - 1);
     e = plan_pass(B, X, N, Y, M, f, g, eps, L.xy, false, nullptr, cost_part, nullptr,
                              nullptr, stream);
@@ -548,7 +477,7 @@ hipError_t launch_emd_backward(int64_t B, int64_t N, int64_t M, const float *X, 
 {
     const EmdLayout L = layout(B, N, M);
     char *base = static_cast<char *>(ws);
-    float *grad_part = reinterpret_cast<float *>(base + L.part_bytes + L.cost_bytes);
+    float *grad_part = reinterpret_cast<float *>(base + L.x4_bytes + L.y4_bytes + L.cost_bytes);
     const float e32 = static_cast<float>(eps);
     hipError_t e = plan_pass(B, X, N, Y, M, f, g, e32, L.xy, true, go, nullptr, grad_part, gX,
                              stream);

@@ -145,3 +145,21 @@ def test_reproducible():
     b = cd.emd_forward(Xg, Yg, 0.5, 0.02, 10)
     for u, v in zip(a, b):
         assert torch.equal(u, v)
+
+
+@pytest.mark.parametrize("B,N,M", [(256, 33, 65), (260, 257, 15), (130, 200, 255), (140, 129, 17),
+                                   (1, 16, 1), (2, 63, 2049), (3, 65, 16)])
+def test_every_split_of_a_half_update_matches_oracle(B, N, M):
+    # 4, 2 and 1 queries per lane (as many as leave 256 workgroups), targets
+    # that leave waves empty, with one target, and with tails.
+    eps = 0.05
+    print(f"[case] emd split B={B} N={N} M={M}", flush=True)
+    X, Y = synth.generate("gmm", B, N, M, 3 * N + M)
+    _, f, g = cd.emd_forward(gc.to_gpu(X), gc.to_gpu(Y), eps, eps, 2)
+    items = sorted({0, B // 2, B - 1})
+    _, F_or, G_or = emd_oracle.sinkhorn(X[items], Y[items], eps, eps, 2)
+    pmax = max(np.abs(F_or).max(), np.abs(G_or).max())
+    # Four half-updates, each non-expansive in the potentials' sup norm.
+    tol = 4 * _step_tol(eps, max(N, M), _cmax(X[items], Y[items]), pmax)
+    assert np.max(np.abs(gc.to_np(f)[items] - F_or)) <= tol
+    assert np.max(np.abs(gc.to_np(g)[items] - G_or)) <= tol
