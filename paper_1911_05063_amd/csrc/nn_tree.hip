@@ -128,6 +128,10 @@ void leaf_search_kernel(SearchArgs a)
     const uint32_t n0 = min(lane, j.t.nodes - 1);
     const float4 nlo = j.t.node[2 * n0], nhi = j.t.node[2 * n0 + 1];
     const float4 q = j.qrec[sub];
+    if (nan_query(q, qhi) && row == 0u) {   // nothing is near it
+        j.dist[__float_as_uint(q.z)] = __builtin_inff();
+        j.idx[__float_as_uint(q.z)] = -1;
+    }
     if (!(qlo.x <= qhi.x)) return;
     const uint32_t id = __float_as_uint(q.w);
 

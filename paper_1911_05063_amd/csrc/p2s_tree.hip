@@ -58,7 +58,7 @@ constexpr uint32_t kFull = kQueue - kWave;
 constexpr int kThreads = 256;
 
 // A face's centroid, to sort by (vertex 0 for a face with a vertex index out
-// of range).
+// of range, 0 for a NaN: such a face may have an edge without one).
 __global__ __launch_bounds__(kThreads) void centroid_kernel(int64_t B, int64_t nv, int64_t nf,
                                                             const float *V, const int32_t *F, float *C)
 {
@@ -73,8 +73,10 @@ __global__ __launch_bounds__(kThreads) void centroid_kernel(int64_t B, int64_t n
 #pragma unroll
         for (int i = 0; i < 3; ++i) v[j][i] = Vb[3 * static_cast<int64_t>(ok ? t[j] : 0) + i];
 #pragma unroll
-    for (int i = 0; i < 3; ++i)
-        C[3 * k + i] = v[0][i] * (1.0f / 3.0f) + v[1][i] * (1.0f / 3.0f) + v[2][i] * (1.0f / 3.0f);
+    for (int i = 0; i < 3; ++i) {
+        const float c = v[0][i] * (1.0f / 3.0f) + v[1][i] * (1.0f / 3.0f) + v[2][i] * (1.0f / 3.0f);
+        C[3 * k + i] = c == c ? c : 0.0f;
+    }
 }
 
 // One node of sorted faces per workgroup, a face per thread: records (eight
@@ -185,6 +187,10 @@ void face_search_kernel(SearchArgs a)
     const uint32_t n0 = min(lane, t.nodes - 1);
     const float4 nlo = t.node[2 * n0], nhi = t.node[2 * n0 + 1];
     const float4 q = a.points[static_cast<int64_t>(n) * kLeaf + sub];
+    if (nan_query(q, qhi) && row == 0u) {   // no face is near it
+        a.dist[b * a.p.n + __float_as_uint(q.z)] = __builtin_inff();
+        a.fidx[b * a.p.n + __float_as_uint(q.z)] = -1;
+    }
     if (!(qlo.x <= qhi.x)) return;
     const uint32_t id = __float_as_uint(q.w);
     const uint32_t active = static_cast<uint32_t>(__ballot(id != kNoPoint)) & 0xffffu;
@@ -264,7 +270,8 @@ void face_search_kernel(SearchArgs a)
     if (id != kNoPoint && row == 0u) {
         const int64_t o = b * a.p.n + id;
         a.dist[o] = high(out);
-        a.fidx[o] = __double2loint(out);
+        // As all pairs: a face whose distance overflows is not chosen.
+        a.fidx[o] = high(out) < __builtin_inff() ? __double2loint(out) : -1;
     }
 }
 

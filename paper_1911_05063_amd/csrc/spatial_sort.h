@@ -22,6 +22,10 @@
 // written.  A leaf is kLeaf slots, a node kNodeLeaves leaves.  Boxes hold the
 // smallest index of their points too; a box without points is empty
 // (lo = +inf, hi = -inf).
+//
+// A point with a NaN coordinate has no distance to anything.  Its slot holds no
+// point (so it is in no box, and no target), but kNanMark as y and its index as
+// z, and its leaf's box says so: the searches answer it at once (nan_query).
 #pragma once
 
 #include <algorithm>
@@ -37,12 +41,13 @@ constexpr int kNode = kLeaf * kNodeLeaves;
 constexpr int kTile = 64;                        // queries of a search wave
 constexpr uint32_t kNoPoint = 0xffffffffu;       // index of a slot without a point
 constexpr float kFarAway = 3.0e38f;              // its x: every squared distance to it is +inf
+constexpr float kNanMark = 1.0f;                 // its y if it stands for a point with a NaN
 
 struct alignas(32) Box {
     float lx, ly, lz;
     uint32_t first;     // smallest index of a point in the box
     float hx, hy, hz;
-    uint32_t pad;
+    uint32_t nans;      // of a leaf: whether it has points with a NaN coordinate
 };
 
 // How one cloud of n points is sorted and stored.
@@ -114,6 +119,13 @@ __device__ __forceinline__ uint32_t wave_min_u32(uint32_t m)
     m = min(r16[0], r16[1]);
     const auto r32 = __builtin_amdgcn_permlane32_swap(m, m, false, false);
     return min(r32[0], r32[1]);
+}
+
+// Whether slot q, of a leaf whose box ends with `hi`, stands for a point with a
+// NaN coordinate (the slots of a leaf without any may be unwritten).
+__device__ __forceinline__ bool nan_query(const float4 &q, const float4 &hi)
+{
+    return __float_as_uint(hi.w) != 0u && __float_as_uint(q.w) == kNoPoint && q.y == kNanMark;
 }
 
 constexpr uint32_t kXcds = 8;       // accelerator complex dies of an MI355X

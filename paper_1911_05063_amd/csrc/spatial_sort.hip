@@ -137,6 +137,14 @@ struct Curve {
 
 namespace {
 
+// How a point (x, y, z, index) is stored: one with a NaN coordinate as a slot
+// without a point that keeps its index aside (spatial_sort.h).
+__device__ __forceinline__ float4 record(const float4 &q)
+{
+    const bool nan = __builtin_isnan(q.x) || __builtin_isnan(q.y) || __builtin_isnan(q.z);
+    return nan ? make_float4(kFarAway, kNanMark, q.w, __uint_as_float(kNoPoint)) : q;
+}
+
 // Exclusive prefix sums over kPer kWave counters per wave of a workgroup of
 // kWaves waves, in place (all threads; total: one entry per wave); returns the
 // sum of all.  Starts and ends with a barrier.
@@ -382,11 +390,12 @@ __device__ __forceinline__ void sort_range(const P3f *__restrict__ pts, const So
         if (held) {
 #pragma unroll
             for (int k = 0; k < kSortHeld; ++k)
-                if (static_cast<uint32_t>(k * kSortThreads + tid) < count) out[cells[(code[k] - low) >> down] + rank[k]] = p[k];
+                if (static_cast<uint32_t>(k * kSortThreads + tid) < count)
+                    out[cells[(code[k] - low) >> down] + rank[k]] = record(p[k]);
         } else {
             for (uint32_t i = tid; i < count; i += kSortThreads) {
                 const float4 q = fetch(i);
-                out[atomicAdd(&cells[(curve.code<kLevels>(q.x, q.y, q.z) - low) >> down], 1u)] = q;
+                out[atomicAdd(&cells[(curve.code<kLevels>(q.x, q.y, q.z) - low) >> down], 1u)] = record(q);
             }
         }
         const uint32_t filled = (count + kTile - 1) / kTile * kTile;
@@ -399,19 +408,21 @@ __device__ __forceinline__ void sort_range(const P3f *__restrict__ pts, const So
         const uint32_t r0 = nd * kNode + lane * kLeaf - start;   // first record of the leaf
         MaxBox b;
         b.clear();
-        uint32_t first = kNoPoint;
+        uint32_t first = kNoPoint, nans = 0u;
         if (r0 < count) {
             const uint32_t m = min(static_cast<uint32_t>(kLeaf), count - r0);
             const float4 *src = out + r0;
 #pragma unroll
             for (uint32_t u = 0; u < kLeaf; ++u) {
                 const float4 q = src[min(u, m - 1)];
-                b.add(q.x, q.y, q.z);
+                const bool point = __float_as_uint(q.w) != kNoPoint;
+                if (point) b.add(q.x, q.y, q.z);
                 first = min(first, __float_as_uint(q.w));
+                nans |= point ? 0u : 1u;
             }
         }
         leaf[static_cast<size_t>(nd) * kNodeLeaves + lane] =
-            Box{-b.v[0], -b.v[1], -b.v[2], first, b.v[3], b.v[4], b.v[5], 0u};
+            Box{-b.v[0], -b.v[1], -b.v[2], first, b.v[3], b.v[4], b.v[5], nans};
 #pragma unroll
         for (int c = 0; c < 6; ++c) b.v[c] = wave_max(b.v[c]);
         first = wave_min_u32(first);

@@ -82,6 +82,14 @@ def _strain(name):
         tri, P = tri * 1e-17, P * 1e-17
     elif name == "huge":
         tri, P = tri * 1e15, P * 1e15
+    elif name == "nan_points":       # single ones, and whole leaves of them
+        P[:, ::41, 1] = np.nan
+        P[:, 20000:30000, 0] = -np.nan
+    elif name == "nan_vertices":     # a corner, so that an edge may be left, or a face
+        tri[:, ::3, 1, 2] = np.nan
+        tri[:, 1::7] = np.nan
+    elif name == "overflow":         # no finite distance: no face
+        P[:, ::50] *= 1e25
     V = tri.reshape(1, -1, 3).astype(np.float32)
     F = np.arange(3 * nf, dtype=np.int32).reshape(1, nf, 3)
     if name == "invalid":
@@ -94,7 +102,8 @@ def _strain(name):
 
 @pytest.mark.parametrize("name", ["plain", "needles", "slivers", "flat", "equal_faces",
                                   "equal_points", "far_points", "outliers", "tiny", "huge",
-                                  "invalid", "all_invalid"])
+                                  "invalid", "all_invalid", "nan_points", "nan_vertices",
+                                  "overflow"])
 def test_strained_meshes_match_all_pairs(name):
     got = _compare(*_strain(name), name)
     if name == "all_invalid":

@@ -90,6 +90,48 @@ def test_strained_clouds_match_all_pairs(name):
     _compare(gc.to_gpu(X), gc.to_gpu(Y), name)
 
 
+def _without(X, Y, fx, fy):
+    """All pairs of the points fx, fy of one item, as the call on all points
+    should give it: +inf and -1 for the others."""
+    ref = _call(X[:, fx].contiguous(), Y[:, fy].contiguous(),
+                cd.workspace_bytes(1, int(fx.sum()), int(fy.sum())))
+    out = []
+    for mine, other, d, i in ((fx, fy, ref[0], ref[1]), (fy, fx, ref[2], ref[3])):
+        dist = torch.full((1, len(mine)), float("inf"), device=X.device)
+        idx = torch.full((1, len(mine)), -1, dtype=torch.int32, device=X.device)
+        dist[:, mine] = d
+        idx[:, mine] = torch.nonzero(other)[:, 0].int()[i.long()]
+        out += [dist, idx]
+    return out
+
+
+# Whole leaves and ranges of points with a NaN, single ones between others
+# (one range and several), of either sign, in each coordinate.
+@pytest.mark.parametrize("N,M", [(30011, 28000), (4001, 180001)])
+@pytest.mark.parametrize("name", ["scattered", "runs", "most", "all_x"])
+def test_nan_points_have_no_neighbour_and_are_none(name, N, M):
+    g = torch.Generator(device="cuda:0").manual_seed(N)
+    X, Y = (2 * torch.rand((1, n, 3), generator=g, device="cuda:0") - 1 for n in (N, M))
+    for P in (X, Y):
+        n = P.shape[1]
+        k = {"scattered": torch.arange(0, n, 37), "runs": torch.arange(n // 3, n // 2),
+             "most": torch.arange(5, n), "all_x": torch.arange(0, n if P is X else 0)}[name]
+        k = k.to(P.device)
+        P[0, k, k % 3] = torch.where(k % 2 == 0, float("nan"), -float("nan"))
+    need, best = cd.workspace_bytes(1, N, M), cd.workspace_bytes_best(1, N, M)
+    assert best > need
+    print(f"[tree] nan {name} N={N} M={M}", flush=True)
+    got = _call(X, Y, best)
+    fx, fy = (torch.isfinite(P[0]).all(dim=1) for P in (X, Y))
+    if name == "all_x":
+        ref = [t for n in (N, M) for t in (torch.full((1, n), float("inf"), device=X.device),
+                                           torch.full((1, n), -1, dtype=torch.int32, device=X.device))]
+    else:
+        ref = _without(X, Y, fx, fy)
+    for what, a, b in zip(("dist_xy", "idx_xy", "dist_yx", "idx_yx"), got, ref):
+        assert torch.equal(a, b), f"{name} {what}: {int((a != b).sum())} differ"
+
+
 def test_entry_points_take_the_same_path_and_bits():
     # Through the binding (default workspace), the static workspace and a graph.
     X_np, Y_np = synth.generate("mesh", 2, 20000, 18001, 5)
