@@ -49,6 +49,10 @@ constexpr int kEBatch = 16;                 // targets per batch of a plan pass
 constexpr int kEMinTB = 64;                 // targets per block, at least
 constexpr int64_t kETargetTiles = 512;
 constexpr int kLseWaves = 16;               // waves of a half-update's workgroup
+// Workgroups of a launch at most: with 2^22 of 1024 threads, 2^32 threads, only
+// some of them run.  (A loop over groups in the kernel: 7.0 -> 8.0 us a
+// half-update of 2 x 500 x 701.)
+constexpr int64_t kLseGrid = 1 << 21;
 constexpr int kLseStep = 16;                // targets per wave: a multiple
 constexpr int64_t kCUs = 256;
 constexpr int kThreads = 256;
@@ -65,6 +69,7 @@ struct LseArgs {
     float out_scale;        // -eps ln 2
     float out_bias;         // eps log(nt)  (= -eps log b)
     int nQG, per;           // query groups per item; targets per wave
+    uint32_t first;         // query group of the launch's first workgroup
 };
 
 __device__ __forceinline__ float dist2(float qx, float qy, float qz, float tx, float ty, float tz)
@@ -103,8 +108,9 @@ __global__ __launch_bounds__(kLseWaves * kWave) void lse_kernel(LseArgs a)
 {
     __shared__ float2 part[kLseWaves][kQ * kWave];
     const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-    const int64_t b = blockIdx.x / a.nQG;
-    const int64_t q0 = static_cast<int64_t>(blockIdx.x % a.nQG) * (kQ * kWave);
+    const uint32_t group = a.first + blockIdx.x;
+    const int64_t b = group / static_cast<uint32_t>(a.nQG);
+    const int64_t q0 = static_cast<int64_t>(group % static_cast<uint32_t>(a.nQG)) * (kQ * kWave);
     float qx[kQ], qy[kQ], qz[kQ], m[kQ], s[kQ];
 #pragma unroll
     for (int k = 0; k < kQ; ++k) {
@@ -384,13 +390,16 @@ void lse_pass(int64_t B, const float *Q, float4 *Q4, int64_t nq, const float4 *T
     const auto groups = [&](int q) { return B * ceil_div(nq, q * kWave); };
     const int q = groups(4) >= kCUs ? 4 : groups(2) >= kCUs ? 2 : 1;
     a.nQG = static_cast<int>(ceil_div(nq, q * kWave));
-    const uint32_t grid = static_cast<uint32_t>(groups(q));
-    if (q == 4)
-        lse_kernel<4, 8><<<grid, kLseWaves * kWave, 0, stream>>>(a);
-    else if (q == 2)
-        lse_kernel<2, 16><<<grid, kLseWaves * kWave, 0, stream>>>(a);
-    else
-        lse_kernel<1, 16><<<grid, kLseWaves * kWave, 0, stream>>>(a);
+    for (int64_t first = 0; first < groups(q); first += kLseGrid) {
+        a.first = static_cast<uint32_t>(first);
+        const uint32_t grid = static_cast<uint32_t>(std::min(groups(q) - first, kLseGrid));
+        if (q == 4)
+            lse_kernel<4, 8><<<grid, kLseWaves * kWave, 0, stream>>>(a);
+        else if (q == 2)
+            lse_kernel<2, 16><<<grid, kLseWaves * kWave, 0, stream>>>(a);
+        else
+            lse_kernel<1, 16><<<grid, kLseWaves * kWave, 0, stream>>>(a);
+    }
 }
 
 hipError_t plan_pass(int64_t B, const float *Q, int64_t nq, const float *T, int64_t nt,

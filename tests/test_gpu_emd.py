@@ -163,3 +163,20 @@ def test_every_split_of_a_half_update_matches_oracle(B, N, M):
     tol = 4 * _step_tol(eps, max(N, M), _cmax(X[items], Y[items]), pmax)
     assert np.max(np.abs(gc.to_np(f)[items] - F_or)) <= tol
     assert np.max(np.abs(gc.to_np(g)[items] - G_or)) <= tol
+
+
+def test_millions_of_tiny_items_match_oracle():
+    # More workgroups than 2^22: a launch holds fewer than 2^32 threads.
+    B, N, M, eps = 4_300_000, 2, 3, 0.1
+    print(f"[case] emd tiny items B={B} N={N} M={M}", flush=True)
+    g = torch.Generator(device="cuda:0").manual_seed(5)
+    X, Y = (torch.rand((B, n, 3), generator=g, device="cuda:0") for n in (N, M))
+    cost, f, gp = cd.emd_forward(X, Y, eps, eps, 2)
+    items = [0, 1, (1 << 20) - 1, 1 << 20, (1 << 22) - 1, 1 << 22, B - 1]
+    Xi, Yi = gc.to_np(X[items]), gc.to_np(Y[items])
+    _, F_or, G_or = emd_oracle.sinkhorn(Xi, Yi, eps, eps, 2)
+    pmax = max(np.abs(F_or).max(), np.abs(G_or).max())
+    tol = 4 * _step_tol(eps, max(N, M), _cmax(Xi, Yi), pmax)
+    assert np.max(np.abs(gc.to_np(f[items]) - F_or)) <= tol
+    assert np.max(np.abs(gc.to_np(gp[items]) - G_or)) <= tol
+    assert bool(torch.isfinite(cost).all())
