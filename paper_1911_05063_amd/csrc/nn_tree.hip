@@ -159,8 +159,6 @@ void leaf_search_kernel(SearchArgs a)
         found[sub] = as_bits(best);
     }
 
-    const uint32_t leaf0 = done[0] != kNoPoint ? done[0] : 0u;   // fills up a list
-
     // 2. The other leaves within the bounds of the box are queued.  Too many
     // (queries far apart, or as far from all targets): a wave each.
     uint32_t queued = 0u;
@@ -175,6 +173,7 @@ void leaf_search_kernel(SearchArgs a)
     // Each query takes those within its own bound to its list; row r visits
     // the lists of queries r, 4 + r, 8 + r and 12 + r, a target per lane.
     __builtin_amdgcn_wave_barrier();
+    const uint32_t fill = queued > 0u ? queue[0] : 0u;   // a leaf with points, to fill a list up
     uint32_t listed[kLeaf / 4];
 #pragma unroll
     for (uint32_t p = 0; p < kLeaf / 4; ++p) listed[p] = 0u;
@@ -204,10 +203,10 @@ void leaf_search_kernel(SearchArgs a)
             for (uint32_t s = 0u; __ballot(s < listed[p]) != 0ull; s += 4u) {
                 const uint4 l = *reinterpret_cast<const uint4 *>(&lists[i][s]);
                 float4 t[4];
-                t[0] = j.rec[(s < listed[p] ? l.x : leaf0) * kLeaf + sub];
-                t[1] = j.rec[(s + 1u < listed[p] ? l.y : leaf0) * kLeaf + sub];
-                t[2] = j.rec[(s + 2u < listed[p] ? l.z : leaf0) * kLeaf + sub];
-                t[3] = j.rec[(s + 3u < listed[p] ? l.w : leaf0) * kLeaf + sub];
+                t[0] = j.rec[(s < listed[p] ? l.x : fill) * kLeaf + sub];
+                t[1] = j.rec[(s + 1u < listed[p] ? l.y : fill) * kLeaf + sub];
+                t[2] = j.rec[(s + 2u < listed[p] ? l.z : fill) * kLeaf + sub];
+                t[3] = j.rec[(s + 3u < listed[p] ? l.w : fill) * kLeaf + sub];
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
                     k = min_key(k, pack(sum_sq(t[v].x - u.x, t[v].y - u.y, t[v].z - u.z),

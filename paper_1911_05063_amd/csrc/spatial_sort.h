@@ -40,7 +40,9 @@ constexpr int kNodeLeaves = 64;
 constexpr int kNode = kLeaf * kNodeLeaves;
 constexpr int kTile = 64;                        // queries of a search wave
 constexpr uint32_t kNoPoint = 0xffffffffu;       // index of a slot without a point
-constexpr float kFarAway = 3.0e38f;              // its x: every squared distance to it is +inf
+// Its x: every squared distance to it is +inf, or NaN from an infinite coordinate
+// (a large finite one would be near points as far out).
+constexpr float kFarAway = __builtin_inff();
 constexpr float kNanMark = 1.0f;                 // its y if it stands for a point with a NaN
 
 struct alignas(32) Box {
@@ -153,10 +155,12 @@ __device__ __forceinline__ double as_key(unsigned long long k)
     return __longlong_as_double(static_cast<long long>(k));
 }
 
+// The smaller key.  The sign is dropped: that of a NaN distance (from infinite
+// coordinates) may be set, and its key is to be above every other.
 __device__ __forceinline__ double min_key(double a, double b)
 {
     double r;
-    asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    asm("v_min_f64 %0, |%1|, |%2|" : "=v"(r) : "v"(a), "v"(b));
     return r;
 }
 

@@ -80,11 +80,16 @@ def _strain(name):
         X, Y = X * 1e-21, Y * 1e-21
     elif name == "huge":              # squared distances near float32's largest
         X, Y = X * 3e18, Y * 3e18
+    elif name in ("at_3e38", "at_max"):   # one coordinate huge and the same: targets around queries
+        Y /= np.linalg.norm(Y[..., 1:], axis=2, keepdims=True)
+        X[..., 0] = Y[..., 0] = 3.0e38 if name == "at_3e38" else -np.finfo(np.float32).max
+        X[..., 1:] *= 0.3
     return X.astype(np.float32), Y.astype(np.float32)
 
 
 @pytest.mark.parametrize("name", ["all_equal", "both_equal", "few_places", "outliers", "line",
-                                  "far_apart", "shell", "lattice", "tiny", "huge"])
+                                  "far_apart", "shell", "lattice", "tiny", "huge", "at_3e38",
+                                  "at_max"])
 def test_strained_clouds_match_all_pairs(name):
     X, Y = _strain(name)
     _compare(gc.to_gpu(X), gc.to_gpu(Y), name)
