@@ -111,10 +111,13 @@ cd_status cd_forward(int64_t B, int64_t N, int64_t M,
  * nothing; the first call on a device looks up that device's array address.
  * Shapes whose cd_workspace_bytes(B, N, M) exceeds the limit (about 8.4
  * million points in B (N + M)) return CD_ERR_WORKSPACE with the sizes in
- * cd_last_error(); use cd_forward for them.  Every call on one GPU shares
+ * cd_last_error(); use cd_forward for them.  Those whose
+ * cd_workspace_bytes_best(B, N, M) exceeds it (about 1.3 million points) take
+ * cd_forward's path for the smaller workspace.  Every call on one GPU shares
  * that GPU's array: calls that overlap in time on one GPU (two streams, two
- * threads) race and give undefined results; calls ordered on one stream, or
- * synchronized, are safe.
+ * threads) race and give undefined distances and indices (the indices are
+ * still -1 or in range, and nothing but the calls' outputs and the array is
+ * written); calls ordered on one stream, or synchronized, are safe.
  */
 #define CD_FORWARD_NOALLOC_MAX_BYTES ((size_t)64 << 20)
 cd_status cd_forward_noalloc(int64_t B, int64_t N, int64_t M,

@@ -71,6 +71,7 @@ struct SearchArgs {
     float *dist[2];
     int32_t *idx[2];
     uint32_t *list;         // [0]: heavy leaves of queries, [1..]: which
+    uint32_t leaves;        // of queries, over items and directions
     SortShape s[2];
 };
 
@@ -82,6 +83,18 @@ struct Job {
     Targets t;
     float *dist;
     int32_t *idx;
+    uint32_t nq, nt;                            // points of the two clouds
+
+    // Query i's neighbour.  Records, leaf numbers and indices are read from
+    // the workspace, which calls that overlap share (cd_forward_noalloc): each is
+    // bounded before it is an address, and an index that leaves the call is
+    // one of a target or -1.
+    __device__ __forceinline__ void store(uint32_t i, float d, uint32_t target) const
+    {
+        if (i >= nq) return;
+        dist[i] = d;
+        idx[i] = target < nt ? static_cast<int32_t>(target) : -1;
+    }
 };
 
 // Whether a box can hold something nearer than `worst` to the box [qlo, qhi],
@@ -110,6 +123,8 @@ __device__ __forceinline__ Job job_of(const SearchArgs &a, uint32_t n)
     j.dist = (k == 0 ? a.dist[0] : a.dist[1]) + b * a.s[k].n;
     j.idx = (k == 0 ? a.idx[0] : a.idx[1]) + b * a.s[k].n;
     j.t.nodes = static_cast<uint32_t>(nt);
+    j.nq = static_cast<uint32_t>(a.s[k].n);
+    j.nt = static_cast<uint32_t>(a.s[1 - k].n);
     return j;
 }
 
@@ -128,10 +143,8 @@ void leaf_search_kernel(SearchArgs a)
     const uint32_t n0 = min(lane, j.t.nodes - 1);
     const float4 nlo = j.t.node[2 * n0], nhi = j.t.node[2 * n0 + 1];
     const float4 q = j.qrec[sub];
-    if (nan_query(q, qhi) && row == 0u) {   // nothing is near it
-        j.dist[__float_as_uint(q.z)] = __builtin_inff();
-        j.idx[__float_as_uint(q.z)] = -1;
-    }
+    if (nan_query(q, qhi) && row == 0u)     // nothing is near it
+        j.store(__float_as_uint(q.z), __builtin_inff(), kNoPoint);
     if (!(qlo.x <= qhi.x)) return;
     const uint32_t id = __float_as_uint(q.w);
 
@@ -167,7 +180,10 @@ void leaf_search_kernel(SearchArgs a)
            [&](const float4 &lo, const float4 &hi) { return within(qlo, qhi, lo, hi, worst, last); },
            [&] { heavy = true; return false; });
     if (heavy) {
-        if (lane == 0u) a.list[1u + atomicAdd(a.list, 1u)] = n;
+        if (lane == 0u) {
+            const uint32_t at = atomicAdd(a.list, 1u);
+            if (at < a.leaves) a.list[1u + at] = n;
+        }
         return;
     }
     // Each query takes those within its own bound to its list; row r visits
@@ -223,8 +239,7 @@ void leaf_search_kernel(SearchArgs a)
     }
     if (id != kNoPoint && row == 0u) {
         best = as_key(found[sub]);
-        j.dist[id] = high(best);
-        j.idx[id] = __double2loint(best);
+        j.store(id, high(best), static_cast<uint32_t>(__double2loint(best)));
     }
 }
 
@@ -234,9 +249,9 @@ void query_search_kernel(SearchArgs a)
 {
     __shared__ uint32_t queue[kQueue];
     const uint32_t lane = threadIdx.x, sub = lane & 15u, row = lane >> 4;
-    const uint32_t items = a.list[0] * kLeaf;
+    const uint32_t items = min(a.list[0], a.leaves) * kLeaf;
     for (uint32_t item = blockIdx.x; item < items; item += gridDim.x) {
-        const Job j = job_of(a, a.list[1u + item / kLeaf]);
+        const Job j = job_of(a, min(a.list[1u + item / kLeaf], a.leaves - 1u));
         const float4 q = j.qrec[item % kLeaf];
         const uint32_t n0 = min(lane, j.t.nodes - 1);
         const float4 nlo = j.t.node[2 * n0], nhi = j.t.node[2 * n0 + 1];
@@ -285,10 +300,7 @@ void query_search_kernel(SearchArgs a)
                [&](const float4 &lo, const float4 &hi) { return within(q, q, lo, hi, worst, last); },
                drain);
         drain();
-        if (lane == 0u) {
-            j.dist[id] = high(best);
-            j.idx[id] = __double2loint(best);
-        }
+        if (lane == 0u) j.store(id, high(best), static_cast<uint32_t>(__double2loint(best)));
     }
 }
 
@@ -344,6 +356,7 @@ hipError_t launch_tree(int64_t B, int64_t N, int64_t M, const FwdArgs &f, hipStr
     s.idx[1] = f.idx_yx;
     const uint32_t leaves = static_cast<uint32_t>(
         B * (static_cast<int64_t>(s.s[0].nodes) + s.s[1].nodes) * kNodeLeaves);
+    s.leaves = leaves;
     leaf_search_kernel<<<leaves, kWave, 0, stream>>>(s);
     query_search_kernel<<<std::min<uint32_t>(leaves * kLeaf, kQueryWaves), kWave, 0, stream>>>(s);
     return hipGetLastError();

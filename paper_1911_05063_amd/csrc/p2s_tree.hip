@@ -91,8 +91,9 @@ __global__ __launch_bounds__(kNode) void face_leaf_kernel(int64_t nv, int64_t nf
     const int64_t nd = blockIdx.x, b = nd / nodes;
     const uint32_t lf = threadIdx.x / kLeaf, sub = threadIdx.x % kLeaf;
     const bool empty = !(leaf[nd * kNodeLeaves + lf].lx <= leaf[nd * kNodeLeaves + lf].hx);
+    // (Read from the workspace: bounded before it is an address.)
     const uint32_t id = empty ? kNoPoint : __float_as_uint(sorted[nd * kNode + threadIdx.x].w);
-    const bool face = id != kNoPoint;
+    const bool face = id < static_cast<uint32_t>(nf);
     const int32_t *t3 = F + (b * nf + (face ? id : 0u)) * 3;
     const int32_t t[3] = {t3[0], t3[1], t3[2]};
     const bool ok = face && face_ok_nb(t, nv);
@@ -187,9 +188,10 @@ void face_search_kernel(SearchArgs a)
     const uint32_t n0 = min(lane, t.nodes - 1);
     const float4 nlo = t.node[2 * n0], nhi = t.node[2 * n0 + 1];
     const float4 q = a.points[static_cast<int64_t>(n) * kLeaf + sub];
-    if (nan_query(q, qhi) && row == 0u) {   // no face is near it
-        a.dist[b * a.p.n + __float_as_uint(q.z)] = __builtin_inff();
-        a.fidx[b * a.p.n + __float_as_uint(q.z)] = -1;
+    const uint32_t np = static_cast<uint32_t>(a.p.n), nf = static_cast<uint32_t>(a.f.n);
+    if (nan_query(q, qhi) && row == 0u && __float_as_uint(q.z) < np) {   // no face is near it
+        a.dist[b * np + __float_as_uint(q.z)] = __builtin_inff();
+        a.fidx[b * np + __float_as_uint(q.z)] = -1;
     }
     if (!(qlo.x <= qhi.x)) return;
     const uint32_t id = __float_as_uint(q.w);
@@ -267,11 +269,12 @@ void face_search_kernel(SearchArgs a)
         out = sub == static_cast<uint32_t>(i) ? k : out;
     }
     out = rows_min(out);
-    if (id != kNoPoint && row == 0u) {
-        const int64_t o = b * a.p.n + id;
+    if (id < np && row == 0u) {
+        const int64_t o = b * np + id;
+        const uint32_t face = static_cast<uint32_t>(__double2loint(out));
         a.dist[o] = high(out);
         // As all pairs: a face whose distance overflows is not chosen.
-        a.fidx[o] = high(out) < __builtin_inff() ? __double2loint(out) : -1;
+        a.fidx[o] = high(out) < __builtin_inff() && face < nf ? static_cast<int32_t>(face) : -1;
     }
 }
 

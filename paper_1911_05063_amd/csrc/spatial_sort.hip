@@ -251,7 +251,9 @@ __device__ __forceinline__ void bucket_chunk(const P3f *__restrict__ pts, const 
     if (tid == 0) o[s.ranges] = count;
 }
 
-// Range w of one cloud.
+// Range w of one cloud.  What it reads back from the workspace (segments,
+// points) is bounded before it is an address: a call that shares the workspace
+// with another may get wrong results, but writes within its own arrays.
 __device__ __forceinline__ void sort_range(const P3f *__restrict__ pts, const SortShape &s, int w,
                                            const float4 *__restrict__ entries,
                                            const uint32_t *__restrict__ offs,
@@ -277,7 +279,8 @@ __device__ __forceinline__ void sort_range(const P3f *__restrict__ pts, const So
         for (int k = 0; k < 2; ++k) {
             const int c = 2 * tid + k;
             const uint32_t *o = offs + static_cast<size_t>(min(c, s.chunks - 1)) * (ranges + 1) + w;
-            const uint32_t a = o[0], e = o[1];
+            const uint32_t held = static_cast<uint32_t>(min(kSortChunk, s.n - min(c, s.chunks - 1) * kSortChunk));
+            const uint32_t a = min(o[0], held), e = min(max(o[1], a), held);
             len[k] = c < s.chunks ? e - a : 0u;
             lower += c < s.chunks ? a : 0u;
             if (c < s.chunks) seg[c] = a;
@@ -297,6 +300,7 @@ __device__ __forceinline__ void sort_range(const P3f *__restrict__ pts, const So
             count += t;
             below += below_total[k];
         }
+        count = min(count, static_cast<uint32_t>(s.n) - min(below, static_cast<uint32_t>(s.n)));
         if (2 * tid < s.chunks) pre[2 * tid] = before;
         if (2 * tid + 1 < s.chunks) pre[2 * tid + 1] = before + len[0];
         if (tid == 0) pre[s.chunks] = count;
@@ -375,6 +379,9 @@ __device__ __forceinline__ void sort_range(const P3f *__restrict__ pts, const So
         low = wave_min_u32(ends[lane % kSortWaves][0]);
         high = ~wave_min_u32(ends[lane % kSortWaves][1]);
         const int down = max(32 - __builtin_clz((high - low) | 1u) - s.log_c, 0);
+        const auto cell = [&](const float4 &q) {
+            return min((curve.code<kLevels>(q.x, q.y, q.z) - low) >> down, static_cast<uint32_t>(ncell) - 1u);
+        };
         if (held) {
 #pragma unroll
             for (int k = 0; k < kSortHeld; ++k)
@@ -382,8 +389,7 @@ __device__ __forceinline__ void sort_range(const P3f *__restrict__ pts, const So
                     rank[k] = atomicAdd(&cells[(code[k] - low) >> down], 1u);
         } else {
             for (uint32_t i = tid; i < count; i += kSortThreads) {
-                const float4 q = fetch(i);
-                atomicAdd(&cells[(curve.code<kLevels>(q.x, q.y, q.z) - low) >> down], 1u);
+                atomicAdd(&cells[cell(fetch(i))], 1u);
             }
         }
         scan_counters<kSortWaves>(cells, scanned, total);
@@ -395,7 +401,7 @@ __device__ __forceinline__ void sort_range(const P3f *__restrict__ pts, const So
         } else {
             for (uint32_t i = tid; i < count; i += kSortThreads) {
                 const float4 q = fetch(i);
-                out[atomicAdd(&cells[(curve.code<kLevels>(q.x, q.y, q.z) - low) >> down], 1u)] = record(q);
+                out[min(atomicAdd(&cells[cell(q)], 1u), count - 1u)] = record(q);
             }
         }
         const uint32_t filled = (count + kTile - 1) / kTile * kTile;
