@@ -78,7 +78,9 @@ __device__ __forceinline__ float dist2(float qx, float qy, float qz, float tx, f
     return __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dx * dx));
 }
 
-// One batch of kB targets for kQ queries: running max m and sum s.
+// One batch of kB targets for kQ queries: running max m and sum s.  The batch
+// is summed by itself, so that no sum has more terms than a batch or than a wave
+// has batches: one by one, terms below 2^-24 of the running sum would be lost.
 template <int kQ, int kB>
 __device__ __forceinline__ void lse_batch(const float (&qx)[kQ], const float (&qy)[kQ],
                                           const float (&qz)[kQ], float (&m)[kQ], float (&s)[kQ],
@@ -95,10 +97,13 @@ __device__ __forceinline__ void lse_batch(const float (&qx)[kQ], const float (&q
             bm = __builtin_fmaxf(bm, z[u]);
         }
         const float mn = __builtin_fmaxf(m[k], bm);
-        float acc = s[k] * __builtin_amdgcn_exp2f(m[k] - mn);
+        // (An FMA at the end in place of the product here: 57 -> 60 us a
+        // half-update of 32 x 2048^2, in every order of the terms.)
+        const float before = s[k] * __builtin_amdgcn_exp2f(m[k] - mn);
+        float acc = 0.0f;
 #pragma unroll
         for (int u = 0; u < kB; ++u) acc += __builtin_amdgcn_exp2f(z[u] - mn);
-        s[k] = acc;
+        s[k] = before + acc;
         m[k] = mn;
     }
 }

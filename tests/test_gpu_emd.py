@@ -180,3 +180,28 @@ def test_millions_of_tiny_items_match_oracle():
     assert np.max(np.abs(gc.to_np(f[items]) - F_or)) <= tol
     assert np.max(np.abs(gc.to_np(gp[items]) - G_or)) <= tol
     assert bool(torch.isfinite(cost).all())
+
+
+@pytest.mark.parametrize("N,M", [(64, 100000), (17, 20001), (600, 40000)])
+def test_few_queries_against_many_targets(N, M):
+    # A few targets at the queries, all others at a distance whose terms are
+    # 2^-24.6 of theirs: added one by one to a running sum they would vanish.
+    # No partial sum may have more than 512 terms: a batch of 16, at most 256
+    # batches, and the merges.
+    eps, terms = 1.0 / (24.6 * np.log(2.0)), 512
+    print(f"[case] emd few queries N={N} M={M}", flush=True)
+    rng = np.random.default_rng(M)
+    X = 1e-4 * rng.uniform(-1, 1, (1, N, 3))
+    Y = rng.normal(size=(1, M, 3))
+    Y /= np.linalg.norm(Y, axis=2, keepdims=True)
+    Y[0, ::5000] *= 1e-4
+    X, Y = X.astype(np.float32), Y.astype(np.float32)
+    g0 = np.zeros((1, M), np.float32)
+    _, f, g = cd.emd_forward(gc.to_gpu(X), gc.to_gpu(Y), eps, eps, 1, g_init=gc.to_gpu(g0))
+    f, g = gc.to_np(f), gc.to_np(g)
+    F_or, _ = emd_oracle.sinkhorn_step(X, Y, g0, eps)
+    tol = _step_tol(eps, terms, 1.0, 0.0)
+    assert np.max(np.abs(f - F_or)) <= tol, (np.max(np.abs(f - F_or)), tol)
+    G_or, _ = emd_oracle.sinkhorn_step(Y, X, f, eps)
+    tol_g = _step_tol(eps, min(N, terms), 1.0, np.abs(f).max())
+    assert np.max(np.abs(g - G_or)) <= tol_g, (np.max(np.abs(g - G_or)), tol_g)
