@@ -17,11 +17,18 @@
 //    batches of targets: the batch maximum rescales the running sum once, then
 //    each pair adds exp2(z - max), z = (g_j - C_ij) log2(e) / eps.  The waves'
 //    (max, sum) meet in LDS and the finished potentials are written, so that a
-//    half-update is one launch and leaves no partials: with the targets split
-//    over workgroups, the next half-update merged the partials of its targets
-//    again in every query group (57.0 us a half-update of 32 x 2048^2 against 54.0,
-//    13.5 against 6.5 on 2 x 500 x 701, 826 against 598 us for 20 iterations of
-//    4 x 300 x 3000).  Queries per lane: as many as leave one workgroup per CU.
+//    half-update is one launch and leaves no partials.  Queries per lane: as
+//    many as leave one workgroup per CU; up to 64 targets take 4 waves, since more
+//    would be idle.  Where one query per lane still leaves CUs idle (few queries,
+//    many targets), the targets are split over workgroups too, and
+//    lse_merge_kernel finishes the potentials.  Per half-update (us; all targets
+//    split over workgroups and merged by every query group of the next
+//    half-update -> no split -> this):
+//      32 x 2048^2      60.0  56.9  57.4      1 x 64 x 100000    127   347  19.6
+//      2 x 500 x 701    14.0   7.0   7.1      1 x 512 x 100000   193   362  36.8
+//      4 x 300 x 3000   20.5  15.0   6.4      1 x 4096^2        36.7  31.1  12.8
+//      1 x 3000 x 30000  110   130  51.3      1 x 8192^2        51.8  60.2  35.0
+//      1000 x 5 x 7     10.6  10.8   4.0      100000 x 10^2      949  1295   238
 //    Bound by instruction issue: 12 instructions a term, two of them
 //    transcendental at about 9 cycles each, 62 cycles per 64 terms.  Measured and
 //    not kept: targets through LDS (6315 against 5420 us for the 50 iterations
@@ -53,7 +60,10 @@ constexpr int kLseWaves = 16;               // waves of a half-update's workgrou
 // some of them run.  (A loop over groups in the kernel: 7.0 -> 8.0 us a
 // half-update of 2 x 500 x 701.)
 constexpr int64_t kLseGrid = 1 << 21;
+constexpr int kLseFew = 4;                  // waves where the targets are few
 constexpr int kLseStep = 16;                // targets per wave: a multiple
+constexpr int kSplitGain = 64;              // targets per wave that a split has to save
+constexpr int kMergeAhead = 16;             // partials loaded together by a merge
 constexpr int64_t kCUs = 256;
 constexpr int kThreads = 256;
 constexpr float kLog2e = 1.4426950408889634f;
@@ -66,9 +76,11 @@ struct LseArgs {
     int64_t nq, nt;
     float k;                // log2(e) / eps
     float k_next;           // that of the next half-update
+    float2 *part;           // [B, nTB, nq] (max, sum) per target block (nTB > 1)
     float out_scale;        // -eps ln 2
     float out_bias;         // eps log(nt)  (= -eps log b)
     int nQG, per;           // query groups per item; targets per wave
+    int nTB, TB;            // target blocks; targets per block
     uint32_t first;         // query group of the launch's first workgroup
 };
 
@@ -108,12 +120,23 @@ __device__ __forceinline__ void lse_batch(const float (&qx)[kQ], const float (&q
     }
 }
 
-template <int kQ, int kB>
-__global__ __launch_bounds__(kLseWaves * kWave) void lse_kernel(LseArgs a)
+// -eps log(b sum exp(...)) of a query from its (max, sum), M and S.
+__device__ __forceinline__ void finish(const LseArgs &a, int64_t at, float M, float S)
 {
-    __shared__ float2 part[kLseWaves][kQ * kWave];
+    const float pot = __builtin_fmaf(a.out_scale, M + __log2f(S), a.out_bias);
+    a.pq[at] = pot;
+    a.Q4[at].w = pot * a.k_next;
+}
+
+// kSplit: the workgroup's targets are one block of nTB, and it leaves (max, sum).
+template <int kQ, int kB, int kWaves, bool kSplit>
+__global__ __launch_bounds__(kWaves * kWave) void lse_kernel(LseArgs a)
+{
+    __shared__ float2 part[kWaves][kQ * kWave];
     const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-    const uint32_t group = a.first + blockIdx.x;
+    const uint32_t tile = a.first + blockIdx.x;
+    const uint32_t tb = kSplit ? tile % static_cast<uint32_t>(a.nTB) : 0u;
+    const uint32_t group = kSplit ? tile / static_cast<uint32_t>(a.nTB) : tile;
     const int64_t b = group / static_cast<uint32_t>(a.nQG);
     const int64_t q0 = static_cast<int64_t>(group % static_cast<uint32_t>(a.nQG)) * (kQ * kWave);
     float qx[kQ], qy[kQ], qz[kQ], m[kQ], s[kQ];
@@ -131,9 +154,11 @@ __global__ __launch_bounds__(kLseWaves * kWave) void lse_kernel(LseArgs a)
     // they arrive by scalar loads.
     const float4 *Tb = a.T + b * a.nt;
     const float kk = a.k;
-    const int nt = static_cast<int>(a.nt);
+    const int t0 = kSplit ? static_cast<int>(tb) * a.TB : 0;
+    const int nt = kSplit ? static_cast<int>(std::min<int64_t>(static_cast<int64_t>(t0) + a.TB, a.nt))
+                          : static_cast<int>(a.nt);
     int j = __builtin_amdgcn_readfirstlane(
-        static_cast<int>(std::min<int64_t>(static_cast<int64_t>(wave) * a.per, nt)));
+        static_cast<int>(std::min<int64_t>(t0 + static_cast<int64_t>(wave) * a.per, nt)));
     const int j1 = static_cast<int>(std::min<int64_t>(static_cast<int64_t>(j) + a.per, nt));
     for (; j + kB <= j1; j += kB) {
         float4 t[kB];
@@ -154,22 +179,48 @@ __global__ __launch_bounds__(kLseWaves * kWave) void lse_kernel(LseArgs a)
 #pragma unroll
     for (int k = 0; k < kQ; ++k) part[wave][k * kWave + lane] = make_float2(m[k], s[k]);
     __syncthreads();
-    // A thread merges one query's (max, sum) of all waves, in order:
-    // -eps log(b sum exp(...)) = scale (M + log2 S) + bias.
+    // A thread merges one query's (max, sum) of all waves, in order.
     const int64_t q = q0 + threadIdx.x;
     if (threadIdx.x >= kQ * kWave || q >= a.nq) return;
-    float2 v[kLseWaves];
+    float2 v[kWaves];
     float M = -__builtin_inff(), S = 0.0f;
 #pragma unroll
-    for (int w = 0; w < kLseWaves; ++w) {
+    for (int w = 0; w < kWaves; ++w) {
         v[w] = part[w][threadIdx.x];
         M = __builtin_fmaxf(M, v[w].x);
     }
 #pragma unroll
-    for (int w = 0; w < kLseWaves; ++w) S += v[w].y * __builtin_amdgcn_exp2f(v[w].x - M);
-    const float pot = __builtin_fmaf(a.out_scale, M + __log2f(S), a.out_bias);
-    a.pq[b * a.nq + q] = pot;
-    a.Q4[b * a.nq + q].w = pot * a.k_next;
+    for (int w = 0; w < kWaves; ++w) S += v[w].y * __builtin_amdgcn_exp2f(v[w].x - M);
+    if (kSplit)
+        a.part[(b * a.nTB + tb) * a.nq + q] = make_float2(M, S);
+    else
+        finish(a, b * a.nq + q, M, S);
+}
+
+// Potentials from the target blocks' (max, sum), in order.
+__global__ __launch_bounds__(kWave) void lse_merge_kernel(LseArgs a, int64_t B)
+{
+    const int64_t k = static_cast<int64_t>(blockIdx.x) * kWave + threadIdx.x;
+    if (k >= B * a.nq) return;
+    const int64_t b = k / a.nq, q = k - b * a.nq;
+    const float2 *p = a.part + b * a.nTB * a.nq + q;
+    float M = -__builtin_inff(), S = 0.0f;
+    for (int t0 = 0; t0 < a.nTB; t0 += kMergeAhead) {
+        // (A block past the last repeats it with weight 0.)
+        float2 v[kMergeAhead];
+        float m = M;
+#pragma unroll
+        for (int u = 0; u < kMergeAhead; ++u) {
+            v[u] = p[std::min(t0 + u, a.nTB - 1) * a.nq];
+            v[u].y = t0 + u < a.nTB ? v[u].y : 0.0f;
+            m = __builtin_fmaxf(m, v[u].x);
+        }
+        S *= __builtin_amdgcn_exp2f(M - m);
+#pragma unroll
+        for (int u = 0; u < kMergeAhead; ++u) S += v[u].y * __builtin_amdgcn_exp2f(v[u].x - m);
+        M = m;
+    }
+    finish(a, k, M, S);
 }
 
 // Both clouds as targets; the y's with their starting potential g (nullptr: 0).
@@ -357,9 +408,43 @@ Tiles tiles_for(int64_t B, int64_t nq, int64_t nt)
     return t;
 }
 
+// How a half-update is split.
+struct LseSplit {
+    int q;          // queries per lane
+    bool few;       // kLseFew waves a workgroup, not kLseWaves
+    int nQG;        // query groups per item
+    int nTB, TB;    // target blocks; targets per block
+    int per;        // targets per wave
+};
+
+// Queries per lane: as many as leave one workgroup per CU and as the item has.
+// Few waves: where more would have no targets.  Target blocks: where even one
+// query per lane leaves CUs idle, as many as fill them, if the targets that this
+// takes from a wave (0.1 us each: four waves on a SIMD, 62 cycles a target) are
+// worth the merge's launch (about 5 us).
+LseSplit split_for(int64_t B, int64_t nq, int64_t nt)
+{
+    LseSplit l{};
+    const auto groups = [&](int q) { return B * ceil_div(nq, q * kWave); };
+    l.q = nq > 2 * kWave && groups(4) >= kCUs ? 4 : nq > kWave && groups(2) >= kCUs ? 2 : 1;
+    l.few = nt <= kLseFew * kLseStep;
+    l.nQG = static_cast<int>(ceil_div(nq, l.q * kWave));
+    const int waves = l.few ? kLseFew : kLseWaves;
+    const auto per = [&](int64_t n) { return ceil_div(ceil_div(n, waves), kLseStep) * kLseStep; };
+    const int64_t blocks = std::min(kCUs / groups(l.q), ceil_div(nt, waves * kLseStep));
+    l.nTB = 1;
+    l.TB = static_cast<int>(nt);
+    if (blocks > 1 && per(nt) - per(ceil_div(nt, blocks)) >= kSplitGain) {
+        l.TB = static_cast<int>(per(ceil_div(nt, blocks)) * waves);
+        l.nTB = static_cast<int>(ceil_div(nt, l.TB));
+    }
+    l.per = static_cast<int>(per(l.TB));
+    return l;
+}
+
 struct EmdLayout {
     Tiles xy, yx;               // plan passes: queries X against Y; queries Y against X
-    size_t x4_bytes, y4_bytes, cost_bytes, grad_bytes;
+    size_t x4_bytes, y4_bytes, part_bytes, cost_bytes, grad_bytes;
 };
 
 EmdLayout layout(int64_t B, int64_t N, int64_t M)
@@ -369,6 +454,11 @@ EmdLayout layout(int64_t B, int64_t N, int64_t M)
     L.yx = tiles_for(B, M, N);
     L.x4_bytes = align256(static_cast<size_t>(B * N) * sizeof(float4));
     L.y4_bytes = align256(static_cast<size_t>(B * M) * sizeof(float4));
+    const auto part = [&](int64_t nq, int64_t nt) {
+        const LseSplit l = split_for(B, nq, nt);
+        return l.nTB > 1 ? static_cast<size_t>(B * l.nTB * nq) * sizeof(float2) : 0;
+    };
+    L.part_bytes = align256(std::max(part(N, M), part(M, N)));
     L.cost_bytes = align256(static_cast<size_t>(B * L.xy.nQG * L.xy.nTB) * 8);
     const size_t g1 = L.xy.nTB > 1 ? static_cast<size_t>(B * L.xy.nTB * N) * 12 : 0;
     const size_t g2 = L.yx.nTB > 1 ? static_cast<size_t>(B * L.yx.nTB * M) * 12 : 0;
@@ -376,35 +466,51 @@ EmdLayout layout(int64_t B, int64_t N, int64_t M)
     return L;
 }
 
+template <bool kSplit>
+void launch_lse(int q, bool few, uint32_t grid, const LseArgs &a, hipStream_t stream)
+{
+    const int waves = few ? kLseFew : kLseWaves;
+    const auto run = [&](auto kernel) { kernel<<<grid, waves * kWave, 0, stream>>>(a); };
+    if (q == 4)
+        run(few ? lse_kernel<4, 8, kLseFew, kSplit> : lse_kernel<4, 8, kLseWaves, kSplit>);
+    else if (q == 2)
+        run(few ? lse_kernel<2, 16, kLseFew, kSplit> : lse_kernel<2, 16, kLseWaves, kSplit>);
+    else
+        run(few ? lse_kernel<1, 16, kLseFew, kSplit> : lse_kernel<1, 16, kLseWaves, kSplit>);
+}
+
 // One half-update of the queries' potentials.
 void lse_pass(int64_t B, const float *Q, float4 *Q4, int64_t nq, const float4 *T, int64_t nt,
-              float *pq, float eps, float eps_next, hipStream_t stream)
+              float *pq, float eps, float eps_next, float2 *part, hipStream_t stream)
 {
+    const LseSplit l = split_for(B, nq, nt);
     LseArgs a{};
     a.Q = Q;
     a.T = T;
     a.Q4 = Q4;
     a.pq = pq;
+    a.part = part;
     a.nq = nq;
     a.nt = nt;
     a.k = kLog2e / eps;
     a.k_next = kLog2e / eps_next;
     a.out_scale = -eps * 0.6931471805599453f;
     a.out_bias = static_cast<float>(static_cast<double>(eps) * std::log(static_cast<double>(nt)));
-    a.per = static_cast<int>(ceil_div(ceil_div(nt, kLseWaves), kLseStep) * kLseStep);
-    const auto groups = [&](int q) { return B * ceil_div(nq, q * kWave); };
-    const int q = groups(4) >= kCUs ? 4 : groups(2) >= kCUs ? 2 : 1;
-    a.nQG = static_cast<int>(ceil_div(nq, q * kWave));
-    for (int64_t first = 0; first < groups(q); first += kLseGrid) {
+    a.per = l.per;
+    a.nQG = l.nQG;
+    a.nTB = l.nTB;
+    a.TB = l.TB;
+    const int64_t tiles = B * l.nQG * l.nTB;
+    for (int64_t first = 0; first < tiles; first += kLseGrid) {
         a.first = static_cast<uint32_t>(first);
-        const uint32_t grid = static_cast<uint32_t>(std::min(groups(q) - first, kLseGrid));
-        if (q == 4)
-            lse_kernel<4, 8><<<grid, kLseWaves * kWave, 0, stream>>>(a);
-        else if (q == 2)
-            lse_kernel<2, 16><<<grid, kLseWaves * kWave, 0, stream>>>(a);
+        const uint32_t grid = static_cast<uint32_t>(std::min(tiles - first, kLseGrid));
+        if (l.nTB > 1)
+            launch_lse<true>(l.q, l.few, grid, a, stream);
         else
-            lse_kernel<1, 16><<<grid, kLseWaves * kWave, 0, stream>>>(a);
+            launch_lse<false>(l.q, l.few, grid, a, stream);
     }
+    if (l.nTB > 1)
+        lse_merge_kernel<<<static_cast<uint32_t>(ceil_div(B * nq, kWave)), kWave, 0, stream>>>(a, B);
 }
 
 hipError_t plan_pass(int64_t B, const float *Q, int64_t nq, const float *T, int64_t nt,
@@ -444,7 +550,7 @@ hipError_t plan_pass(int64_t B, const float *Q, int64_t nq, const float *T, int6
 size_t emd_workspace_bytes(int64_t B, int64_t N, int64_t M)
 {
     const EmdLayout L = layout(B, N, M);
-    return L.x4_bytes + L.y4_bytes + L.cost_bytes + L.grad_bytes;
+    return L.x4_bytes + L.y4_bytes + L.part_bytes + L.cost_bytes + L.grad_bytes;
 }
 
 float emd_eps(double eps_start, double eps_end, int n_iters, int t)
@@ -463,15 +569,16 @@ hipError_t launch_emd_forward(int64_t B, int64_t N, int64_t M, const float *X, c
     char *base = static_cast<char *>(ws);
     float4 *X4 = reinterpret_cast<float4 *>(base);
     float4 *Y4 = reinterpret_cast<float4 *>(base + L.x4_bytes);
-    double *cost_part = reinterpret_cast<double *>(base + L.x4_bytes + L.y4_bytes);
+    float2 *part = reinterpret_cast<float2 *>(base + L.x4_bytes + L.y4_bytes);
+    double *cost_part = reinterpret_cast<double *>(base + L.x4_bytes + L.y4_bytes + L.part_bytes);
     targets_kernel<<<static_cast<uint32_t>(ceil_div(B * (N + M), kThreads)), kThreads, 0, stream>>>(
         B * N, B * M, X, Y, warm ? g : nullptr, kLog2e / emd_eps(eps_start, eps_end, n_iters, 0), X4, Y4);
     hipError_t e;
     for (int t = 0; t < n_iters; ++t) {
         const float eps = emd_eps(eps_start, eps_end, n_iters, t);
         const float next = emd_eps(eps_start, eps_end, n_iters, std::min(t + 1, n_iters - 1));
-        lse_pass(B, X, X4, N, Y4, M, f, eps, eps, stream);
-        lse_pass(B, Y, Y4, M, X4, N, g, eps, next, stream);
+        lse_pass(B, X, X4, N, Y4, M, f, eps, eps, part, stream);
+        lse_pass(B, Y, Y4, M, X4, N, g, eps, next, part, stream);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -491,7 +598,8 @@ hipError_t launch_emd_backward(int64_t B, int64_t N, int64_t M, const float *X, 
 {
     const EmdLayout L = layout(B, N, M);
     char *base = static_cast<char *>(ws);
-    float *grad_part = reinterpret_cast<float *>(base + L.x4_bytes + L.y4_bytes + L.cost_bytes);
+    float *grad_part = reinterpret_cast<float *>(base + L.x4_bytes + L.y4_bytes + L.part_bytes +
+                                                 L.cost_bytes);
     const float e32 = static_cast<float>(eps);
     hipError_t e = plan_pass(B, X, N, Y, M, f, g, e32, L.xy, true, go, nullptr, grad_part, gX,
                              stream);

@@ -205,3 +205,21 @@ def test_few_queries_against_many_targets(N, M):
     G_or, _ = emd_oracle.sinkhorn_step(Y, X, f, eps)
     tol_g = _step_tol(eps, min(N, terms), 1.0, np.abs(f).max())
     assert np.max(np.abs(g - G_or)) <= tol_g, (np.max(np.abs(g - G_or)), tol_g)
+
+
+@pytest.mark.parametrize("B,N,M", [(1, 64, 1537), (1, 65, 20001), (2, 513, 4097), (1, 4097, 300),
+                                   (300, 70, 64), (256, 129, 65), (1, 7, 65537)])
+def test_split_targets_match_oracle(B, N, M):
+    # Few queries: the targets are split over workgroups, with remainders in
+    # the last block and in its waves; up to 64 targets: four waves.
+    eps = 0.05
+    print(f"[case] emd target split B={B} N={N} M={M}", flush=True)
+    X, Y = synth.generate("gmm", B, N, M, N + 3 * M)
+    _, f, g = cd.emd_forward(gc.to_gpu(X), gc.to_gpu(Y), eps, eps, 2)
+    items = sorted({0, B // 2, B - 1})
+    _, F_or, G_or = emd_oracle.sinkhorn(X[items], Y[items], eps, eps, 2)
+    pmax = max(np.abs(F_or).max(), np.abs(G_or).max())
+    # Four half-updates, each non-expansive; sums of at most 512 terms.
+    tol = 4 * _step_tol(eps, 512, _cmax(X[items], Y[items]), pmax)
+    assert np.max(np.abs(gc.to_np(f)[items] - F_or)) <= tol
+    assert np.max(np.abs(gc.to_np(g)[items] - G_or)) <= tol
