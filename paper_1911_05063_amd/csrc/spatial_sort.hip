@@ -20,6 +20,12 @@ constexpr int kRangePoints = 1536;               // points per range aimed at ab
 constexpr int kMaxChunks = 1024;                 // per cloud (LDS segment table)
 constexpr int kLogCells = 13;                    // cells per range at most: 32 KB of LDS counters
 constexpr int kLevels = 10;                      // curve levels within a range
+// A cell with more of a cloud's samples, or with a larger share of a range's
+// points (and more of them), is crowded: the grid does not resolve the cloud.
+// (From 62 samples on, mixtures of 4 x 100000 x 10000 points took the warp, which
+// costs the sort about 13 us, for nothing: 177 -> 213 us.)
+constexpr uint32_t kCrowdSamples = kSortSamples / 8;
+constexpr uint32_t kCrowdSixteenths = 7, kCrowdPoints = 16 * kLeaf;
 static_assert(static_cast<int64_t>(kMaxChunks) * kSortChunk == kSortMaxPoints, "segment table");
 
 struct P3f {
@@ -42,12 +48,14 @@ __device__ __forceinline__ uint32_t wave_scan_u32(uint32_t v)
 // Index along the Hilbert curve of a cell of the 2^kLevels cube (kLevels bits
 // per axis), after Skilling, "Programming the Hilbert curve" (2004): the axes
 // are turned level by level, then Gray-decoded and interleaved.  Neighbours on
-// the curve are neighbours in space, which curve index order is not at its jumps:
-// the searches visit about half as many leaves.
-template <int kLevels>
+// the curve are neighbours in space, which those of a Z-order curve are not at
+// its jumps: the searches visit about half as many leaves.
+// (kUnroll 1: a loop, for paths that few clouds take, so that they don't grow
+// the usual path's code.)
+template <int kLevels, int kUnroll = kLevels>
 __device__ __forceinline__ uint32_t hilbert(uint32_t x, uint32_t y, uint32_t z)
 {
-#pragma unroll
+#pragma unroll kUnroll
     for (int l = kLevels - 1; l > 0; --l) {
         const uint32_t low = (1u << l) - 1u;
         const auto bit = [&](uint32_t v) { return 0u - ((v >> l) & 1u); };   // all ones if set
@@ -63,13 +71,13 @@ __device__ __forceinline__ uint32_t hilbert(uint32_t x, uint32_t y, uint32_t z)
     y ^= x;
     z ^= y;
     uint32_t t = 0u;
-#pragma unroll
+#pragma unroll kUnroll
     for (int l = kLevels - 1; l > 0; --l) t ^= ((1u << l) - 1u) & (0u - ((z >> l) & 1u));
     x ^= t;
     y ^= t;
     z ^= t;
     uint32_t code = 0u;
-#pragma unroll
+#pragma unroll kUnroll
     for (int l = kLevels - 1; l >= 0; --l)
         code = code << 3 | ((x >> l) & 1u) << 2 | ((y >> l) & 1u) << 1 | ((z >> l) & 1u);
     return code;
@@ -107,21 +115,84 @@ struct MaxBox {
     }
 };
 
+// A grid of 2^kLevels cells per axis between quantiles of 64 samples: the
+// points between one and the next (a sixteenth of them) share 64 equal cells.
+// The outermost quantiles reach at most eight times as far as their
+// neighbours; points beyond belong to border cells.  For clouds that a regular
+// grid does not resolve: a few points far from all others, padding at a place of
+// its own, several scales.
+constexpr int kKnots = 16;
+constexpr int kPerKnot = (1 << kLevels) / kKnots;
+
+struct Warp {
+    float knot[3][kKnots], scale[3][kKnots];    // lower ends of the intervals, cells per unit
+
+    __device__ __forceinline__ uint32_t cell(int axis, float p) const
+    {
+        const float *k = knot[axis];
+        int i = p >= k[8] ? 8 : 0;
+        i += p >= k[i + 4] ? 4 : 0;
+        i += p >= k[i + 2] ? 2 : 0;
+        i += p >= k[i + 1] ? 1 : 0;
+        return static_cast<uint32_t>(i * kPerKnot) +
+               static_cast<uint32_t>(__builtin_amdgcn_fmed3f((p - k[i]) * scale[axis][i], 0.0f,
+                                                             static_cast<float>(kPerKnot - 1)));
+    }
+
+    // One axis from the wave's 64 samples (one per lane; NaN: past all others).
+    __device__ __forceinline__ void set(int axis, float v)
+    {
+        const int lane = threadIdx.x % kWave;
+        v = v == v ? v : __builtin_inff();
+#pragma unroll
+        for (int k = 2; k <= kWave; k <<= 1)
+#pragma unroll
+            for (int j = k >> 1; j > 0; j >>= 1) {
+                const float o = __shfl_xor(v, j, kWave);
+                v = ((lane & j) == 0) == ((lane & k) == 0) ? fminf(v, o) : fmaxf(v, o);
+            }
+        const auto at = [&](int i) { return __shfl(v, i, kWave); };
+        const float least = fmaxf(at(0), at(4) - 8.0f * (at(8) - at(4)));
+        const float most = fminf(at(63), at(60) + 8.0f * (at(60) - at(56)));
+        const float q = __shfl(v, 4 * (lane % kKnots), kWave);
+        const float next = __shfl(v, min(4 * (lane % kKnots) + 4, kWave - 1), kWave);
+        const float lo = lane == 0 ? least : q, hi = lane == kKnots - 1 ? most : next;
+        if (lane < kKnots) {
+            const float width = hi - lo;
+            knot[axis][lane] = lo;
+            scale[axis][lane] = width > 0.0f ? static_cast<float>(kPerKnot) / width : 0.0f;
+        }
+    }
+};
+
 }  // namespace
 
-// Curve indices in a box, 2^kLevels cells over its longest side, to any number
-// of levels (fewer levels give the leading bits).  Any value, NaN included,
-// gives an index.
+// Curve indices in a box, 2^kLevels cells over its longest side, or in a warped
+// grid, to any number of levels (fewer levels give the leading bits).  Any
+// value, NaN included, gives an index.
 struct Curve {
     float lo[3], scale;     // cells per unit at kLevels levels
-    Curve() = default;
-    __device__ __forceinline__ explicit Curve(const MaxBox &b)
+    uint32_t warped;        // the grid is w instead
+    Warp w;
+    __device__ __forceinline__ void box(const MaxBox &b)
     {
         lo[0] = -b.v[0];
         lo[1] = -b.v[1];
         lo[2] = -b.v[2];
         const float ext = fmaxf(b.v[3] + b.v[0], fmaxf(b.v[4] + b.v[1], b.v[5] + b.v[2]));
         scale = ext > 0.0f ? static_cast<float>(1 << kLevels) / ext : 0.0f;
+    }
+};
+
+namespace {
+
+// A curve's box in registers; the warp stays where it is.
+struct Grid {
+    float lo[3], scale;
+    const Warp *w;
+    __device__ __forceinline__ explicit Grid(const Curve &c)
+        : lo{c.lo[0], c.lo[1], c.lo[2]}, scale(c.scale), w(&c.w)
+    {
     }
     template <int kTo>
     __device__ __forceinline__ uint32_t code(float x, float y, float z) const
@@ -133,9 +204,13 @@ struct Curve {
         };
         return hilbert<kTo>(cell(x, lo[0]), cell(y, lo[1]), cell(z, lo[2]));
     }
+    template <int kTo>
+    __device__ __forceinline__ uint32_t warped(float x, float y, float z) const
+    {
+        constexpr int kDown = kLevels - kTo;
+        return hilbert<kTo, 1>(w->cell(0, x) >> kDown, w->cell(1, y) >> kDown, w->cell(2, z) >> kDown);
+    }
 };
-
-namespace {
 
 // How a point (x, y, z, index) is stored: one with a NaN coordinate as a slot
 // without a point that keeps its index aside (spatial_sort.h).
@@ -189,6 +264,12 @@ __device__ __forceinline__ uint32_t scan_counters(uint32_t *cells, int n, uint32
     return scan_counters<kWaves, 16>(cells, total);
 }
 
+// Where sample k of kSortSamples is in a cloud that ends with point `last`.
+__device__ __forceinline__ uint64_t sample_at(int k, int last)
+{
+    return static_cast<uint64_t>(k) * static_cast<uint32_t>(last) / (kSortSamples - 1);
+}
+
 // Points of one chunk grouped by range: entries (x, y, z, index) and, per
 // range, the first of its entries (one more offset ends the last range).
 __device__ __forceinline__ void bucket_chunk(const P3f *__restrict__ pts, const SortShape &s,
@@ -201,13 +282,15 @@ __device__ __forceinline__ void bucket_chunk(const P3f *__restrict__ pts, const 
     __shared__ uint32_t hist[kMaxRanges];
     __shared__ float red[kBucketThreads / kWave][6];
     __shared__ uint32_t total[kBucketThreads / kWave];
+    __shared__ Curve curve;
+    __shared__ uint32_t crowded;
+    __shared__ uint16_t codes[kBucketHeld][kBucketThreads];      // of a warped curve
     const int tid = threadIdx.x;
     const int first = chunk * kSortChunk, last = s.n - 1;
     P3f p[kBucketHeld], sample[kPerThread];
 #pragma unroll
     for (int k = 0; k < kPerThread; ++k)
-        sample[k] = pts[static_cast<uint64_t>(k * kBucketThreads + tid) * static_cast<uint32_t>(last) /
-                        (kSortSamples - 1)];
+        sample[k] = pts[sample_at(k * kBucketThreads + tid, last)];
 #pragma unroll
     for (int k = 0; k < kBucketHeld; ++k) p[k] = pts[min(first + k * kBucketThreads + tid, last)];
     for (int r = tid; r < kMaxRanges; r += kBucketThreads) hist[r] = 0u;
@@ -216,23 +299,56 @@ __device__ __forceinline__ void bucket_chunk(const P3f *__restrict__ pts, const 
     box.clear();
 #pragma unroll
     for (int k = 0; k < kPerThread; ++k) box.add(sample[k].x, sample[k].y, sample[k].z);
+    if (tid == 0) crowded = 0u;
     box.group<kBucketThreads / kWave>(red);
-    const Curve curve(box);
-    if (chunk == 0 && tid == 0) *shared_curve = curve;
+    if (tid == 0) {
+        curve.box(box);
+        curve.warped = 0u;
+    }
+    __syncthreads();
+    const Grid grid(curve);
 #pragma unroll
     for (int k = 0; k < kPerThread; ++k)
-        atomicAdd(&share[curve.code<kRangeLevels>(sample[k].x, sample[k].y, sample[k].z)], 1u);
+        if (atomicAdd(&share[grid.code<kRangeLevels>(sample[k].x, sample[k].y, sample[k].z)], 1u) >= kCrowdSamples)
+            crowded = 1u;
+    __syncthreads();
+    const bool warped = __builtin_amdgcn_readfirstlane(crowded) != 0u;
+    if (warped) {
+        if (tid < 3 * kWave)
+            curve.w.set(tid / kWave, reinterpret_cast<const float *>(
+                                         pts + static_cast<uint64_t>(tid % kWave) * static_cast<uint32_t>(last) /
+                                                   (kWave - 1))[tid / kWave]);
+        if (tid == 0) curve.warped = 1u;
+        for (int r = tid; r < kRangeCells; r += kBucketThreads) share[r] = 0u;
+        __syncthreads();
+        // (Loops that are not unrolled, on reloaded points: the code of the
+        // usual path stays small.)
+#pragma unroll 1
+        for (int k = 0; k < kPerThread; ++k) {
+            const P3f q = pts[sample_at(k * kBucketThreads + tid, last)];
+            atomicAdd(&share[grid.warped<kRangeLevels>(q.x, q.y, q.z)], 1u);
+        }
+#pragma unroll 1
+        for (int k = 0; k < kBucketHeld; ++k) {
+            const P3f q = pts[min(first + k * kBucketThreads + tid, last)];
+            codes[k][tid] = static_cast<uint16_t>(grid.warped<kRangeLevels>(q.x, q.y, q.z));
+        }
+    }
+    if (chunk == 0)
+        for (uint32_t k = tid; k < sizeof(Curve) / 4; k += kBucketThreads)
+            reinterpret_cast<uint32_t *>(shared_curve)[k] = reinterpret_cast<const uint32_t *>(&curve)[k];
     scan_counters<kBucketThreads / kWave>(share, kRangeCells, total);
     // A cell whose samples follow t others belongs to range t ranges / samples.
-    // A cell of four ranges' worth of samples or more (many equal points) is
-    // dealt out by index: its points' order says nothing anyway.
+    // A cell of four ranges' worth of samples or more (in a warped grid one and a
+    // half: many equal points) is dealt out by index.
+    const uint32_t deal = warped ? 3 * kSortSamples / 2 : 4 * kSortSamples;
     uint32_t range[kBucketHeld], rank[kBucketHeld];
 #pragma unroll
     for (int k = 0; k < kBucketHeld; ++k) {
         const int i = first + k * kBucketThreads + tid;
-        const uint32_t c = curve.code<kRangeLevels>(p[k].x, p[k].y, p[k].z);
+        const uint32_t c = warped ? codes[k][tid] : grid.code<kRangeLevels>(p[k].x, p[k].y, p[k].z);
         const uint32_t t = share[c], own = (c + 1 < kRangeCells ? share[c + 1] : kSortSamples) - t;
-        const uint32_t dealt = own * s.ranges >= 4 * kSortSamples
+        const uint32_t dealt = own * s.ranges >= deal
                                    ? (static_cast<uint32_t>(i) * 2654435761u >> 16) * own >> 16 : 0u;
         range[k] = min((t + dealt) * s.ranges / kSortSamples, static_cast<uint32_t>(s.ranges) - 1u);
         if (i <= last) rank[k] = atomicAdd(&hist[range[k]], 1u);
@@ -265,6 +381,8 @@ __device__ __forceinline__ void sort_range(const P3f *__restrict__ pts, const So
     __shared__ uint32_t pre[kMaxChunks + 1], seg[kMaxChunks];
     __shared__ float red[kSortWaves][6];
     __shared__ uint32_t total[kSortWaves], below_total[kSortWaves], ends[kSortWaves][2];
+    __shared__ Curve curve;
+    __shared__ uint32_t crowded;
     const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
     const int ncell = 1 << s.log_c, ranges = s.ranges;
     const bool one = ranges == 1;
@@ -325,7 +443,6 @@ __device__ __forceinline__ void sort_range(const P3f *__restrict__ pts, const So
     if (count > 0u) {
         const bool held = count <= kSortHeld * kSortThreads;
         float4 p[kSortHeld];
-        Curve curve;
         if (held) {
 #pragma unroll
             for (int k = 0; k < kSortHeld; ++k)
@@ -337,60 +454,104 @@ __device__ __forceinline__ void sort_range(const P3f *__restrict__ pts, const So
         if (one) {
             MaxBox box;
             box.clear();
-            if (held) {
 #pragma unroll
-                for (int k = 0; k < kSortHeld; ++k) box.add(p[k].x, p[k].y, p[k].z);
-            } else {
-                for (uint32_t i = tid; i < count; i += kSortThreads) {
-                    const float4 q = fetch(i);
-                    box.add(q.x, q.y, q.z);
-                }
-            }
+            for (int k = 0; k < kSortHeld; ++k) box.add(p[k].x, p[k].y, p[k].z);
             box.group<kSortWaves>(red);
-            curve = Curve(box);
-        } else {
-            curve = *shared_curve;
+            if (tid == 0) {
+                curve.box(box);
+                curve.warped = 0u;
+            }
+        } else if (tid < static_cast<int>(sizeof(Curve) / 4)) {
+            reinterpret_cast<uint32_t *>(&curve)[tid] = reinterpret_cast<const uint32_t *>(shared_curve)[tid];
         }
+        if (tid == 0) crowded = 0u;
+        __syncthreads();
+        const Grid grid(curve);
+        bool warped = __builtin_amdgcn_readfirstlane(curve.warped) != 0u;
         // The range's codes from the lowest on, in as many cells as there are.
         uint32_t code[kSortHeld], rank[kSortHeld], low = kNoPoint, high = 0u;
-        if (held) {
-#pragma unroll
-            for (int k = 0; k < kSortHeld; ++k) {
-                if (static_cast<uint32_t>(k * kSortThreads) >= count) continue;
-                code[k] = curve.code<kLevels>(p[k].x, p[k].y, p[k].z);
-                low = min(low, code[k]);
-                high = max(high, code[k]);
-            }
-        } else {
-            for (uint32_t i = tid; i < count; i += kSortThreads) {
-                const float4 q = fetch(i);
-                const uint32_t c = curve.code<kLevels>(q.x, q.y, q.z);
-                low = min(low, c);
-                high = max(high, c);
-            }
-        }
-        low = wave_min_u32(low);
-        high = ~wave_min_u32(~high);
-        if (lane == 0) {
-            ends[wave][0] = low;
-            ends[wave][1] = ~high;
-        }
-        __syncthreads();
-        low = wave_min_u32(ends[lane % kSortWaves][0]);
-        high = ~wave_min_u32(ends[lane % kSortWaves][1]);
-        const int down = max(32 - __builtin_clz((high - low) | 1u) - s.log_c, 0);
-        const auto cell = [&](const float4 &q) {
-            return min((curve.code<kLevels>(q.x, q.y, q.z) - low) >> down, static_cast<uint32_t>(ncell) - 1u);
+        int down = 0;
+        const auto code_of = [&](const float4 &q) {
+            return warped ? grid.warped<kLevels>(q.x, q.y, q.z) : grid.code<kLevels>(q.x, q.y, q.z);
         };
-        if (held) {
+        const auto cell = [&](const float4 &q) {
+            return min((code_of(q) - low) >> down, static_cast<uint32_t>(ncell) - 1u);
+        };
+        const auto span = [&] {     // low, high of the workgroup
+            low = wave_min_u32(low);
+            high = ~wave_min_u32(~high);
+            if (lane == 0) {
+                ends[wave][0] = low;
+                ends[wave][1] = ~high;
+            }
+            __syncthreads();
+            low = wave_min_u32(ends[lane % kSortWaves][0]);
+            high = ~wave_min_u32(ends[lane % kSortWaves][1]);
+            down = max(32 - __builtin_clz((high - low) | 1u) - s.log_c, 0);
+        };
+        const uint32_t crowd = max(count * kCrowdSixteenths / 16u, kCrowdPoints);
+        const auto rank_held = [&] {    // codes -> ranks within cells; notes a crowded one
 #pragma unroll
             for (int k = 0; k < kSortHeld; ++k)
-                if (static_cast<uint32_t>(k * kSortThreads + tid) < count)
+                if (static_cast<uint32_t>(k * kSortThreads) < count) {
+                    low = min(low, code[k]);
+                    high = max(high, code[k]);
+                }
+            span();
+            bool full = false;
+#pragma unroll
+            for (int k = 0; k < kSortHeld; ++k)
+                if (static_cast<uint32_t>(k * kSortThreads + tid) < count) {
                     rank[k] = atomicAdd(&cells[(code[k] - low) >> down], 1u);
-        } else {
-            for (uint32_t i = tid; i < count; i += kSortThreads) {
-                atomicAdd(&cells[cell(fetch(i))], 1u);
+                    full |= rank[k] >= crowd;
+                }
+            if (full) crowded = 1u;
+            __syncthreads();
+        };
+        bool done = false;
+        if (held && !warped) {
+#pragma unroll
+            for (int k = 0; k < kSortHeld; ++k)
+                if (static_cast<uint32_t>(k * kSortThreads) < count)
+                    code[k] = grid.code<kLevels>(p[k].x, p[k].y, p[k].z);
+            rank_held();
+            done = __builtin_amdgcn_readfirstlane(crowded) == 0u;
+        }
+        // Otherwise: many points, a warped curve, or a crowded cell, which takes
+        // the range's own quantiles.  (Apart from the usual path, which a loop
+        // around both made 8 us slower.)
+        for (bool own = false; !done;) {
+            if (!own && __builtin_amdgcn_readfirstlane(crowded) != 0u) {
+                own = warped = true;
+                if (wave < 3) {
+                    const float4 q = fetch(static_cast<uint32_t>(lane) * (count - 1u) / (kWave - 1u));
+                    curve.w.set(wave, wave == 0 ? q.x : wave == 1 ? q.y : q.z);
+                }
+                for (int c = tid; c < scanned; c += kSortThreads) cells[c] = 0u;
+                __syncthreads();
             }
+            low = kNoPoint;
+            high = 0u;
+            if (held) {
+#pragma unroll
+                for (int k = 0; k < kSortHeld; ++k)
+                    if (static_cast<uint32_t>(k * kSortThreads) < count)
+                        code[k] = grid.warped<kLevels>(p[k].x, p[k].y, p[k].z);
+                rank_held();
+            } else {
+                for (uint32_t i = tid; i < count; i += kSortThreads) {
+                    const uint32_t c = code_of(fetch(i));
+                    low = min(low, c);
+                    high = max(high, c);
+                }
+                span();
+                bool full = false;
+                for (uint32_t i = tid; i < count; i += kSortThreads)
+                    full |= atomicAdd(&cells[cell(fetch(i))], 1u) >= crowd;
+                if (full) crowded = 1u;
+                __syncthreads();
+            }
+            done = own || __builtin_amdgcn_readfirstlane(crowded) == 0u;
         }
         scan_counters<kSortWaves>(cells, scanned, total);
         if (held) {
