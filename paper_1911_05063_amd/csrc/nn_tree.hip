@@ -70,10 +70,22 @@ struct SearchArgs {
     const float4 *rec[2], *leaf[2], *node[2];
     float *dist[2];
     int32_t *idx[2];
-    uint32_t *list;         // [0]: heavy leaves of queries, [1..]: which
+    uint32_t *list;         // heavy leaves of queries (below)
     uint32_t leaves;        // of queries, over items and directions
     SortShape s[2];
 };
+
+// The list of heavy leaves: kStripes lists, leaf n in list n % kStripes, so that
+// the waves that add to them seldom meet at one counter (10 ns each time; 32768
+// heavy leaves with one counter: 380 us).  Their lengths, kStride words apart,
+// then their entries.
+constexpr uint32_t kStripes = kWave;
+constexpr uint32_t kStride = 32;
+
+__host__ __device__ __forceinline__ uint32_t stripe_room(uint32_t leaves)
+{
+    return (leaves + kStripes - 1) / kStripes;
+}
 
 // A leaf of queries (numbered over items, directions and leaves) and the cloud
 // they search.
@@ -178,11 +190,12 @@ void leaf_search_kernel(SearchArgs a)
     bool heavy = false;
     gather(j.t, nlo, nhi, lane, done, queue, queued, kSplit,
            [&](const float4 &lo, const float4 &hi) { return within(qlo, qhi, lo, hi, worst, last); },
-           [&] { heavy = true; return false; });
+           [&](uint32_t, uint32_t) { heavy = true; return false; });
     if (heavy) {
         if (lane == 0u) {
-            const uint32_t at = atomicAdd(a.list, 1u);
-            if (at < a.leaves) a.list[1u + at] = n;
+            const uint32_t s = n % kStripes, room = stripe_room(a.leaves);
+            const uint32_t at = atomicAdd(a.list + s * kStride, 1u);
+            if (at < room) a.list[kStripes * kStride + s * room + at] = n;
         }
         return;
     }
@@ -249,9 +262,19 @@ void query_search_kernel(SearchArgs a)
 {
     __shared__ uint32_t queue[kQueue];
     const uint32_t lane = threadIdx.x, sub = lane & 15u, row = lane >> 4;
-    const uint32_t items = min(a.list[0], a.leaves) * kLeaf;
+    // Lane l: the entries of lists 0 to l.
+    const uint32_t room = stripe_room(a.leaves);
+    uint32_t upto = min(a.list[lane * kStride], room);
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) {
+        const uint32_t o = __shfl_up(upto, d, kWave);
+        upto += lane >= static_cast<uint32_t>(d) ? o : 0u;
+    }
+    const uint32_t items = __builtin_amdgcn_readlane(upto, kWave - 1) * kLeaf;
     for (uint32_t item = blockIdx.x; item < items; item += gridDim.x) {
-        const Job j = job_of(a, min(a.list[1u + item / kLeaf], a.leaves - 1u));
+        const uint32_t s = __popcll(__ballot(upto <= item / kLeaf));
+        const uint32_t at = item / kLeaf - (s > 0u ? __builtin_amdgcn_readlane(upto, s - 1u) : 0u);
+        const Job j = job_of(a, min(a.list[kStripes * kStride + s * room + at], a.leaves - 1u));
         const float4 q = j.qrec[item % kLeaf];
         const uint32_t n0 = min(lane, j.t.nodes - 1);
         const float4 nlo = j.t.node[2 * n0], nhi = j.t.node[2 * n0 + 1];
@@ -281,7 +304,7 @@ void query_search_kernel(SearchArgs a)
             settle();
         }
         uint32_t queued = 0u;
-        const auto drain = [&] {
+        const auto drain = [&](uint32_t, uint32_t) {
             __builtin_amdgcn_wave_barrier();
             for (uint32_t c = 0u; c < queued; c += 16u) {
                 float4 t[4];
@@ -299,7 +322,7 @@ void query_search_kernel(SearchArgs a)
         gather(j.t, nlo, nhi, lane, done, queue, queued, kDrain,
                [&](const float4 &lo, const float4 &hi) { return within(q, q, lo, hi, worst, last); },
                drain);
-        drain();
+        drain(0u, 0u);
         if (lane == 0u) j.store(id, high(best), static_cast<uint32_t>(__double2loint(best)));
     }
 }
@@ -318,8 +341,8 @@ TreeLayout layout(int64_t B, int64_t N, int64_t M)
     l.sort[0] = plan_sort(B, N, at);
     l.sort[1] = plan_sort(B, M, at);
     l.list = at;
-    l.bytes = at + align256(4 * (1 + static_cast<size_t>(B) * (l.sort[0].s.nodes + l.sort[1].s.nodes) *
-                                         kNodeLeaves));
+    const size_t leaves = static_cast<size_t>(B) * (l.sort[0].s.nodes + l.sort[1].s.nodes) * kNodeLeaves;
+    l.bytes = at + align256(4 * kStripes * (kStride + (leaves + kStripes - 1) / kStripes));
     return l;
 }
 
@@ -342,7 +365,7 @@ hipError_t launch_tree(int64_t B, int64_t N, int64_t M, const FwdArgs &f, hipStr
     const SortJob job[2] = {sort_job(l.sort[0], f.X, base), sort_job(l.sort[1], f.Y, base)};
     SearchArgs s{};
     s.list = reinterpret_cast<uint32_t *>(base + l.list);
-    const hipError_t e = launch_sort(B, job[0], job[1], s.list, stream);
+    const hipError_t e = launch_sort(B, job[0], job[1], s.list, kStripes * kStride, stream);
     if (e != hipSuccess) return e;
     for (int k = 0; k < 2; ++k) {
         s.rec[k] = job[k].rec;

@@ -236,7 +236,7 @@ void face_search_kernel(SearchArgs a)
     nearest_leaves(t, qlo, qhi, nlo, nhi, lane, done);
     if (lane < 4u) queue[lane] = done[0] == kNoPoint ? 0u : lane == 0u ? done[0] : lane == 1u ? done[1] : lane == 2u ? done[2] : done[3];
     uint32_t queued = done[0] != kNoPoint ? 4u : 0u;
-    const auto drain = [&]() __attribute__((always_inline)) {
+    const auto drain = [&](uint32_t, uint32_t) __attribute__((always_inline)) {
         __builtin_amdgcn_wave_barrier();
         for (uint32_t c = 0u; c < queued; c += 4u) {
             const uint32_t leaf = queue[min(c + row, queued - 1u)];
@@ -253,7 +253,7 @@ void face_search_kernel(SearchArgs a)
         return true;
     };
     for (bool first = true;; first = false) {
-        drain();
+        drain(0u, 0u);
         if (!first) break;
         gather(t, nlo, nhi, lane, done, queue, queued, kFull,
                [&](const float4 &lo, const float4 &hi) { return reaches(qlo, qhi, lo, hi, worst); }, drain);
@@ -282,7 +282,7 @@ size_t align256(size_t x) { return (x + 255) & ~static_cast<size_t>(255); }
 
 struct TreeLayout {
     SortPlan points, faces;
-    size_t centroids, rec, counter, bytes;
+    size_t centroids, rec, bytes;
 };
 
 TreeLayout layout(int64_t B, int64_t S, int64_t nf)
@@ -295,8 +295,7 @@ TreeLayout layout(int64_t B, int64_t S, int64_t nf)
     at += align256(static_cast<size_t>(B) * nf * 12);
     l.rec = at;
     at += align256(static_cast<size_t>(B) * l.faces.s.nodes * kNode * kRec * 4);
-    l.counter = at;
-    l.bytes = at + 256;
+    l.bytes = at;
     return l;
 }
 
@@ -321,7 +320,7 @@ hipError_t launch_p2s_tree(int64_t B, int64_t S, int64_t nv, int64_t nf, const f
     centroid_kernel<<<static_cast<uint32_t>((B * nf + kThreads - 1) / kThreads), kThreads, 0, stream>>>(
         B, nv, nf, V, F, centroids);
     const SortJob pj = sort_job(l.points, P, base), fj = sort_job(l.faces, centroids, base);
-    const hipError_t e = launch_sort(B, pj, fj, reinterpret_cast<uint32_t *>(base + l.counter), stream);
+    const hipError_t e = launch_sort(B, pj, fj, nullptr, 0u, stream);
     if (e != hipSuccess) return e;
     float4 *rec = reinterpret_cast<float4 *>(base + l.rec);
     face_leaf_kernel<<<static_cast<uint32_t>(B * fj.s.nodes), kNode, 0, stream>>>(

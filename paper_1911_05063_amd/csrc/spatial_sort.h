@@ -91,8 +91,8 @@ constexpr int64_t kSortMaxPoints = int64_t{1} << 21;
 // Lays the sorted clouds out from byte `at` on, which it moves past them.
 SortPlan plan_sort(int64_t B, int64_t n, size_t &at);
 SortJob sort_job(const SortPlan &p, const float *P, char *ws);
-// Sorts two batches of B clouds in the same launches and zeroes *counter.
-hipError_t launch_sort(int64_t B, const SortJob &a, const SortJob &b, uint32_t *counter,
+// Sorts two batches of B clouds in the same launches and zeroes n words.
+hipError_t launch_sort(int64_t B, const SortJob &a, const SortJob &b, uint32_t *zero, uint32_t n,
                        hipStream_t stream);
 
 template <int kCtrl>
@@ -309,15 +309,17 @@ __device__ __forceinline__ void append(uint32_t *list, uint32_t &n, bool take, u
 }
 
 // Queues the leaves, other than the four done, that takes(lo, hi) of their box
-// (and of their node's) lets pass.  full() is called when more than `limit` are
-// queued and ends the walk by returning false; it may empty the queue and
-// tighten what takes() lets pass.
+// (and of their node's) lets pass.  full(walked, ahead) is called when more than
+// `limit` are queued, with the nodes walked and those to walk still, and ends
+// the walk by returning false; it may empty the queue and tighten what takes()
+// lets pass.
 template <class Takes, class Full>
 __device__ __forceinline__ void gather(const Targets &j, const float4 &nlo, const float4 &nhi,
                                        uint32_t lane, const uint32_t done[4], uint32_t *queue,
                                        uint32_t &queued, uint32_t limit, const Takes &takes,
                                        const Full &full)
 {
+    uint32_t walked = 0u;
     for (uint32_t from = 0; from < j.nodes; from += kWave) {
         float4 lo = nlo, hi = nhi;
         if (from > 0u) {
@@ -331,11 +333,14 @@ __device__ __forceinline__ void gather(const Targets &j, const float4 &nlo, cons
             if (left == 0ull) break;
             const uint32_t at = (from + __builtin_ctzll(left)) * kNodeLeaves + lane;
             left &= left - 1ull;
+            ++walked;
             bool take = takes(j.leaf[at * 2], j.leaf[at * 2 + 1]);
 #pragma unroll
             for (int v = 0; v < 4; ++v) take = take && done[v] != at;
             append(queue, queued, take, at);
-            if (queued > limit && !full()) return;
+            if (queued > limit &&
+                !full(walked, static_cast<uint32_t>(__popcll(left)) + (j.nodes - min(from + kWave, j.nodes))))
+                return;
         }
     }
 }

@@ -599,7 +599,8 @@ __device__ __forceinline__ void sort_range(const P3f *__restrict__ pts, const So
 
 struct SortArgs {
     SortJob job[2];
-    uint32_t *counter;
+    uint32_t *zero;
+    uint32_t n;
 };
 
 __global__ __launch_bounds__(kBucketThreads) void bucket_kernel(SortArgs a)
@@ -618,7 +619,8 @@ __global__ __launch_bounds__(kBucketThreads) void bucket_kernel(SortArgs a)
 
 __global__ __launch_bounds__(kSortThreads) void sort_kernel(SortArgs a)
 {
-    if (blockIdx.x == 0 && threadIdx.x == 0) *a.counter = 0u;
+    if (blockIdx.x == 0)
+        for (uint32_t k = threadIdx.x; k < a.n; k += kSortThreads) a.zero[k] = 0u;
     const uint32_t wg = xcd_block();
     const uint32_t w0 = a.job[0].s.ranges, w1 = a.job[1].s.ranges;
     const int64_t b = wg / (w0 + w1);
@@ -681,10 +683,10 @@ SortJob sort_job(const SortPlan &p, const float *P, char *ws)
     return j;
 }
 
-hipError_t launch_sort(int64_t B, const SortJob &a, const SortJob &b, uint32_t *counter,
+hipError_t launch_sort(int64_t B, const SortJob &a, const SortJob &b, uint32_t *zero, uint32_t n,
                        hipStream_t stream)
 {
-    const SortArgs args{{a, b}, counter};
+    const SortArgs args{{a, b}, zero, n};
     if (a.s.ranges > 1 || b.s.ranges > 1)
         bucket_kernel<<<static_cast<uint32_t>(B * (static_cast<int64_t>(a.s.chunks) + b.s.chunks)),
                         kBucketThreads, 0, stream>>>(args);
