@@ -201,7 +201,7 @@ void leaf_search_kernel(SearchArgs a)
     }
     // Each query takes those within its own bound to its list; row r visits
     // the lists of queries r, 4 + r, 8 + r and 12 + r, a target per lane.
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
     const uint32_t fill = queued > 0u ? queue[0] : 0u;   // a leaf with points, to fill a list up
     uint32_t listed[kLeaf / 4];
 #pragma unroll
@@ -223,7 +223,7 @@ void leaf_search_kernel(SearchArgs a)
             full |= listed[p] > kList - kLeaf;
         }
         if (__ballot(full) == 0ull) continue;
-        __builtin_amdgcn_wave_barrier();
+        wave_sync();
 #pragma unroll
         for (uint32_t p = 0; p < kLeaf / 4; ++p) {
             const uint32_t i = p * 4 + row;
@@ -248,7 +248,7 @@ void leaf_search_kernel(SearchArgs a)
             if (sub == 0u) found[i] = as_bits(k);
             listed[p] = 0u;
         }
-        __builtin_amdgcn_wave_barrier();
+        wave_sync();
     }
     if (id != kNoPoint && row == 0u) {
         best = as_key(found[sub]);
@@ -305,7 +305,7 @@ void query_search_kernel(SearchArgs a)
         }
         uint32_t queued = 0u;
         const auto drain = [&](uint32_t, uint32_t) {
-            __builtin_amdgcn_wave_barrier();
+            wave_sync();
             for (uint32_t c = 0u; c < queued; c += 16u) {
                 float4 t[4];
 #pragma unroll
@@ -316,7 +316,7 @@ void query_search_kernel(SearchArgs a)
             }
             if (queued > 0u) settle();
             queued = 0u;
-            __builtin_amdgcn_wave_barrier();
+            wave_sync();
             return true;
         };
         gather(j.t, nlo, nhi, lane, done, queue, queued, kDrain,

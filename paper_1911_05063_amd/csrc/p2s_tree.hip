@@ -237,7 +237,7 @@ void face_search_kernel(SearchArgs a)
     if (lane < 4u) queue[lane] = done[0] == kNoPoint ? 0u : lane == 0u ? done[0] : lane == 1u ? done[1] : lane == 2u ? done[2] : done[3];
     uint32_t queued = done[0] != kNoPoint ? 4u : 0u;
     const auto drain = [&](uint32_t, uint32_t) __attribute__((always_inline)) {
-        __builtin_amdgcn_wave_barrier();
+        wave_sync();
         for (uint32_t c = 0u; c < queued; c += 4u) {
             const uint32_t leaf = queue[min(c + row, queued - 1u)];
             const float4 lo = t.leaf[leaf * 2], hi = t.leaf[leaf * 2 + 1];
@@ -249,7 +249,7 @@ void face_search_kernel(SearchArgs a)
             settle();
         }
         queued = 0u;
-        __builtin_amdgcn_wave_barrier();
+        wave_sync();
         return true;
     };
     for (bool first = true;; first = false) {

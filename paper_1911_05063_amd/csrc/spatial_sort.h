@@ -298,6 +298,15 @@ __device__ __forceinline__ void nearest_leaves(const Targets &j, const float4 &q
     }
 }
 
+// What lanes of a wave wrote to LDS before this, others may read after it.  (A
+// wave's LDS operations execute in order; the fence keeps the compiler from
+// moving them, or from taking accesses of other types for unrelated.)
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // Appends v of the lanes that take it to a list of n values in LDS.
 __device__ __forceinline__ void append(uint32_t *list, uint32_t &n, bool take, uint32_t v)
 {
