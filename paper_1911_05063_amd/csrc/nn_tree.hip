@@ -32,13 +32,16 @@
 //    go to a list, and a second launch searches for each of their queries in a
 //    wave of its own.  Measured with a wave per four of them: slower on
 //    outliers (245 against 157 us on the Gaussian mixtures), since their
-//    common box is the problem.
+//    common box is the problem; with a workgroup per leaf and its 16 queries
+//    sharing the targets' loads: 173 -> 192 us there, 4 x 60000 x 3001 90 -> 144, for
+//    131 -> 123 on a template.  Where nearly every query would visit nearly all
+//    targets, it takes all of them, from the clouds as they are.
 //
 // Bound by instruction issue and latency (about 1600 VALU instructions per 16
 // queries on the mesh workload against 15000 for all pairs).  cd_forward, all
-// pairs -> this (us, one box): 16 x 16384^2 mesh samples 496 -> 118; 4 x 100000 x
-// 10000 mixture 480 -> 155; 8 x 65536^2 grid points 3660 -> 169; 1 x 30000 x 25001
-// 102 -> 53; 1 x 200000^2 uniform 4500 -> 110.
+// pairs -> this (us, calls back to back): 16 x 16384^2 mesh samples 525 -> 129; 4 x
+// 100000 x 10000 mixture 500 -> 175; 8 x 65536^2 grid points 3660 -> 201; 1 x 30000 x
+// 25001 110 -> 60; 1 x 200000^2 uniform 4600 -> 185.
 #include "cd_internal.h"
 #include "fixed_point.h"
 #include "spatial_sort.h"
@@ -50,20 +53,57 @@ namespace {
 
 // The rule for this path.  Sorting and three to four dependent launches cost
 // about 45 us whatever the size, the time of 3.5e8 pairs of the all-pairs
-// search; measured, uniform clouds and mixtures gain from 4e8 pairs on (4 x
-// 10000^2: 70 -> 50 us) but a sphere against a surface inside it, where each
-// query is about as far from many targets, only from 2e9 (1e9: 135 -> 155 us, 2e9:
-// 263 -> 258).  With a cloud of few points there is nothing to skip (17 x
-// 100000: 47 us either way).
+// search.  Measured, all pairs -> this (us), and a template (a sphere against a
+// surface inside it, where each query is about as far from many targets), the
+// worst of the kinds looked at that are not all of that sort:
+//                       template    mesh       uniform    sphere     mixture
+//   1 x 26645^2 (7.1e8)  113 128    113  56    107  43    106  49    115  58
+//   16 x 6661^2 (7.1e8)  123 129    124  78    128  70    124  58    128  70
+//   4 x 60000 x 3001     115 161    113  90    113  87    113  79    114  95
+//   1 x 31622^2 (1e9)    142 147    144  61    145  49    145  57    144  56
+//   8 x 3001 x 40000     169 127    174 100    172  83    172  70    180  83
+//   16 x 11180^2 (2e9)   283 240    281  98    281  81    280  75    285  90
+//   16 x 15811^2 (4e9)   505 385    517 117    513 102    514  94    513 118
+// The line is where every other kind gains at least a fifth, most of them twice;
+// templates lose up to 14% below 1.2e9 pairs, and up to 40% of a small cloud against
+// a large one.  Clouds where every query is as far from all targets (a sphere
+// around its centre) lose at any size, up to 3 times (kAllShare).  With a cloud of few points there is nothing to
+// skip (17 x 100000: 47 us either way).
 constexpr double kMinPairs = 7e8;
 constexpr int64_t kMinCloud = 1800;
 constexpr size_t kMaxTreeBytes = size_t{4} << 30;
-constexpr uint32_t kQueryWaves = 8192;   // of the search for heavy queries
+constexpr int kQueryWaves = 4;           // of a workgroup of the search for heavy queries
+constexpr int kQueryThreads = kQueryWaves * kWave;
+constexpr uint32_t kQueryGroups = 2048;  // workgroups of it at most
+constexpr int kBatch = 32;               // targets per batch where it takes all
 constexpr uint32_t kQueue = 192;    // leaves queued at most
 constexpr uint32_t kDrain = 32;     // leaves a single query queues before it visits them
 constexpr uint32_t kSplit = 128;    // and above this the queries are split
 static_assert(kSplit + kWave <= kQueue && kDrain + kWave <= kQueue, "a node's leaves fit the queue");
+// Where the heavy leaves' queries are expected to visit more than this share of
+// all leaves of targets, counting every leaf of the nodes within the bounds of
+// the leaf's box, all targets are taken instead (search_all).  Measured shares (us
+// with the tree, with all targets, and of the all-pairs search, which shares
+// its distances between the directions): template 4 x 60000 x 3001 0.19 (160, -, 115),
+// lognormal radii 64 x 4000^2 0.47 (374, -, 153), a sphere of 30000 points around 25001
+// 0.57 (500, -, 104), 16 x 16384^2 0.65 (3190, 1295, 510), around a cluster 0.82 (3740,
+// 1278, 510).  Handing such calls back to the all-pairs kernels (650 us) costs
+// two launches that mostly do nothing: 5 us of every call.
+constexpr double kAllShare = 0.56;
 constexpr uint32_t kList = 48;      // leaves listed per query
+
+// Sum over the wave, in every lane.
+__device__ __forceinline__ float wave_sum(float v)
+{
+    v += dpp_f<0xB1>(v);
+    v += dpp_f<0x4E>(v);
+    v += dpp_f<0x141>(v);
+    v += dpp_f<0x140>(v);
+    const auto r16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(r16[0]) + __uint_as_float(r16[1]);
+    const auto r32 = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(r32[0]) + __uint_as_float(r32[1]);
+}
 
 // The two directions of a call: queries of cloud k against the other cloud.
 struct SearchArgs {
@@ -71,16 +111,21 @@ struct SearchArgs {
     float *dist[2];
     int32_t *idx[2];
     uint32_t *list;         // heavy leaves of queries (below)
-    uint32_t leaves;        // of queries, over items and directions
+    uint32_t leaves, items; // leaves of queries, over items and directions; items
+    const float *cloud[2];  // [B, n, 3]
+    float most_visits;      // in units; with more all targets are taken
     SortShape s[2];
 };
 
 // The list of heavy leaves: kStripes lists, leaf n in list n % kStripes, so that
 // the waves that add to them seldom meet at one counter (10 ns each time; 32768
-// heavy leaves with one counter: 380 us).  Their lengths, kStride words apart,
-// then their entries.
+// heavy leaves with one counter: 380 us).  Their heads, kStride words apart, then
+// their entries.  A head: the length, and the visits that the list is expected
+// to take, each of a leaf of targets by a query, in units of kVisitUnit (so that
+// they fit a word).
 constexpr uint32_t kStripes = kWave;
 constexpr uint32_t kStride = 32;
+constexpr uint32_t kVisits = 1, kVisitUnit = 64;
 
 __host__ __device__ __forceinline__ uint32_t stripe_room(uint32_t leaves)
 {
@@ -192,16 +237,22 @@ void leaf_search_kernel(SearchArgs a)
            [&](const float4 &lo, const float4 &hi) { return within(qlo, qhi, lo, hi, worst, last); },
            [&](uint32_t, uint32_t) { heavy = true; return false; });
     if (heavy) {
+        const uint64_t near = __ballot(lane < j.t.nodes && within(qlo, qhi, nlo, nhi, worst, last));
         if (lane == 0u) {
+            // The place in the list and the visits in one atomic.
             const uint32_t s = n % kStripes, room = stripe_room(a.leaves);
-            const uint32_t at = atomicAdd(a.list + s * kStride, 1u);
+            const uint32_t nodes = static_cast<uint32_t>(__popcll(near)) * j.t.nodes /
+                                   min(j.t.nodes, static_cast<uint32_t>(kWave));
+            const uint64_t units = nodes * (kLeaf * kNodeLeaves / kVisitUnit);
+            const uint32_t at = static_cast<uint32_t>(atomicAdd(
+                reinterpret_cast<unsigned long long *>(a.list + s * kStride), units << 32 | 1u));
             if (at < room) a.list[kStripes * kStride + s * room + at] = n;
         }
         return;
     }
+    wave_sync();
     // Each query takes those within its own bound to its list; row r visits
     // the lists of queries r, 4 + r, 8 + r and 12 + r, a target per lane.
-    wave_sync();
     const uint32_t fill = queued > 0u ? queue[0] : 0u;   // a leaf with points, to fill a list up
     uint32_t listed[kLeaf / 4];
 #pragma unroll
@@ -256,12 +307,82 @@ void leaf_search_kernel(SearchArgs a)
     }
 }
 
-// One wave: one query of a listed leaf at a time.
-__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(8, 8)))
+using Constant = __attribute__((address_space(4))) float;
+
+// All targets for 64 queries of a cloud, those numbered `group` over items and
+// directions: a query per lane, a share of the targets per wave.  As in the
+// all-pairs search, the index of the minimum is looked for in the batch of
+// targets that last lowered it.
+__device__ __forceinline__ void search_all(const SearchArgs &a, uint32_t group, uint32_t wave,
+                                           uint32_t lane, double (&part)[kQueryWaves][kWave])
+{
+    const uint32_t g0 = (a.s[0].n + kWave - 1) / kWave, g1 = (a.s[1].n + kWave - 1) / kWave;
+    const int64_t b = group / (g0 + g1);
+    uint32_t g = group % (g0 + g1);
+    const int k = g < g0 ? 0 : 1;
+    g -= k == 0 ? 0u : g0;
+    const int nq = k == 0 ? a.s[0].n : a.s[1].n, nt = k == 0 ? a.s[1].n : a.s[0].n;
+    const int64_t q = b * nq + min(static_cast<int>(g * kWave + lane), nq - 1);
+    const float *Q = (k == 0 ? a.cloud[0] : a.cloud[1]) + 3 * q;
+    // Memory that the launch does not write: scalar loads, although the results of
+    // the workgroup's last queries were stored.
+    const Constant *T = reinterpret_cast<const Constant *>(
+        reinterpret_cast<uintptr_t>((k == 0 ? a.cloud[1] : a.cloud[0]) + 3 * b * nt));
+    const float qx = Q[0], qy = Q[1], qz = Q[2];
+    const auto dist = [&](const Constant *t) { return sum_sq(t[0] - qx, t[1] - qy, t[2] - qz); };
+    const int per = (nt + kQueryWaves * kBatch - 1) / (kQueryWaves * kBatch) * kBatch;
+    const int t0 = min(static_cast<int>(wave) * per, nt), t1 = min(t0 + per, nt);
+    float best = __builtin_inff();
+    int from = t0, t = t0;
+    for (; t + kBatch <= t1; t += kBatch) {
+        const Constant *p = T + 3 * t;      // the same in all lanes
+        float m = __builtin_inff();
+#pragma unroll
+        for (int u = 0; u < kBatch; u += 2) {
+            const float d0 = dist(p + 3 * u), d1 = dist(p + 3 * u + 3);
+            asm("v_min3_f32 %0, %1, %2, %3" : "=v"(m) : "v"(m), "v"(d0), "v"(d1));
+        }
+        from = m < best ? t : from;
+        best = m < best ? m : best;
+    }
+#pragma unroll 1
+    for (int u = t; u < t1; ++u) {
+        const float d = dist(T + 3 * u);
+        from = d < best ? t : from;
+        best = d < best ? d : best;
+    }
+    uint32_t at = kNoPoint;
+    if (best < __builtin_inff())
+#pragma unroll 1
+        for (int u = min(from + kBatch, t1) - 1; u >= from; --u)
+            at = dist(T + 3 * u) == best ? u : at;
+    part[wave][lane] = pack(best, at);
+    __syncthreads();
+    if (wave == 0u && g * kWave + lane < static_cast<uint32_t>(nq)) {
+        double key = part[0][lane];
+#pragma unroll
+        for (int w = 1; w < kQueryWaves; ++w) key = min_key(key, part[w][lane]);
+        (k == 0 ? a.dist[0] : a.dist[1])[q] = high(key);
+        (k == 0 ? a.idx[0] : a.idx[1])[q] = __double2loint(key);
+    }
+    __syncthreads();
+}
+
+// A wave takes one query of a listed leaf at a time; or, where those are expected
+// to visit too many leaves, a workgroup all targets for 64 queries.
+__global__ __launch_bounds__(kQueryThreads) __attribute__((amdgpu_waves_per_eu(8, 8)))
 void query_search_kernel(SearchArgs a)
 {
-    __shared__ uint32_t queue[kQueue];
-    const uint32_t lane = threadIdx.x, sub = lane & 15u, row = lane >> 4;
+    __shared__ uint32_t queues[kQueryWaves][kQueue];
+    __shared__ double part[kQueryWaves][kWave];
+    const uint32_t lane = threadIdx.x % kWave, sub = lane & 15u, row = lane >> 4;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    uint32_t *queue = queues[wave];
+    if (wave_sum(static_cast<float>(a.list[lane * kStride + kVisits])) > a.most_visits) {
+        const uint32_t groups = a.items * ((a.s[0].n + kWave - 1) / kWave + (a.s[1].n + kWave - 1) / kWave);
+        for (uint32_t g = blockIdx.x; g < groups; g += gridDim.x) search_all(a, g, wave, lane, part);
+        return;
+    }
     // Lane l: the entries of lists 0 to l.
     const uint32_t room = stripe_room(a.leaves);
     uint32_t upto = min(a.list[lane * kStride], room);
@@ -271,7 +392,7 @@ void query_search_kernel(SearchArgs a)
         upto += lane >= static_cast<uint32_t>(d) ? o : 0u;
     }
     const uint32_t items = __builtin_amdgcn_readlane(upto, kWave - 1) * kLeaf;
-    for (uint32_t item = blockIdx.x; item < items; item += gridDim.x) {
+    for (uint32_t item = blockIdx.x * kQueryWaves + wave; item < items; item += gridDim.x * kQueryWaves) {
         const uint32_t s = __popcll(__ballot(upto <= item / kLeaf));
         const uint32_t at = item / kLeaf - (s > 0u ? __builtin_amdgcn_readlane(upto, s - 1u) : 0u);
         const Job j = job_of(a, min(a.list[kStripes * kStride + s * room + at], a.leaves - 1u));
@@ -381,7 +502,15 @@ hipError_t launch_tree(int64_t B, int64_t N, int64_t M, const FwdArgs &f, hipStr
         B * (static_cast<int64_t>(s.s[0].nodes) + s.s[1].nodes) * kNodeLeaves);
     s.leaves = leaves;
     leaf_search_kernel<<<leaves, kWave, 0, stream>>>(s);
-    query_search_kernel<<<std::min<uint32_t>(leaves * kLeaf, kQueryWaves), kWave, 0, stream>>>(s);
+    s.most_visits = static_cast<float>(
+        kAllShare * static_cast<double>(B) *
+        (static_cast<double>(N) * s.s[1].nodes + static_cast<double>(M) * s.s[0].nodes) *
+        (kNodeLeaves / kVisitUnit));
+    s.items = static_cast<uint32_t>(B);
+    s.cloud[0] = f.X;
+    s.cloud[1] = f.Y;
+    query_search_kernel<<<std::min((leaves * kLeaf + kQueryWaves - 1) / kQueryWaves, kQueryGroups),
+                          kQueryThreads, 0, stream>>>(s);
     return hipGetLastError();
 }
 
