@@ -233,7 +233,7 @@ void leaf_search_kernel(SearchArgs a)
     // (queries far apart, or as far from all targets): a wave each.
     uint32_t queued = 0u;
     bool heavy = false;
-    gather(j.t, nlo, nhi, lane, done, queue, queued, kSplit,
+    gather(j.t, nlo, nhi, lane, done, queue, queued, kSplit, true,
            [&](const float4 &lo, const float4 &hi) { return within(qlo, qhi, lo, hi, worst, last); },
            [&](uint32_t, uint32_t) { heavy = true; return false; });
     if (heavy) {
@@ -440,7 +440,7 @@ void query_search_kernel(SearchArgs a)
             wave_sync();
             return true;
         };
-        gather(j.t, nlo, nhi, lane, done, queue, queued, kDrain,
+        gather(j.t, nlo, nhi, lane, done, queue, queued, kDrain, true,
                [&](const float4 &lo, const float4 &hi) { return within(q, q, lo, hi, worst, last); },
                drain);
         drain(0u, 0u);

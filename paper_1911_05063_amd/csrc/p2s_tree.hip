@@ -31,8 +31,8 @@
 //    The four leaves nearest to the points come first, then the others within
 //    the bounds of the points' box.
 //
-// Measured (us, one box, all pairs -> this): 16 x 16384 points against 5120 faces
-// 1266 -> 155, 3 x 50001 against 1922 341 -> 76, 16 x 10000 against 7200 1064 -> 146.
+// Measured (us, all pairs -> this): 16 x 16384 points against 5120 faces 1266 ->
+// 148, 16 x 11284 against 7200 1347 -> 154.
 // The search itself takes 109 us of the first: about 4500 VALU instructions per
 // 16 points, issue bound at three waves per SIMD (163 VGPRs; four waves spill
 // and take 10 us more).
@@ -45,16 +45,31 @@ namespace cdk {
 namespace {
 
 // The rule for this path.  The sort and the records cost about 45 us, the time
-// of 5e7 pairs of the all-pairs search; from 1.5e8 pairs on closed and open
-// surfaces gain twice that and more (8 x 4096 points, 5120 faces: 193 -> 75 us).
-// With few faces these are large against the distances, and boxes around them
-// skip little: 2000 random triangles 566 -> 602 us, 1000 137 -> 193; meshes below
-// 2048 faces keep all pairs.
+// of 5e7 pairs of the all-pairs search; from 1.5e8 pairs on surfaces gain twice
+// that and more.  Boxes around few, large triangles skip little, and meshes below
+// 2048 faces keep all pairs (2000 random triangles 566 -> 602 us, 1000 137 -> 193);
+// a height field of 1922 faces would gain (3 x 50001 points 341 -> 76).  Large
+// triangles in any number, and points near the centre of a closed surface, are
+// about as far from all faces, and lose: 15 to 40% where there are many points,
+// up to twice where the sort is a large part.  Measured (us, all pairs -> this):
+//                        icosphere  grid       small soup  large soup  points inside
+//   1.6e8 pairs, 1 item   189  58    188  78    208  84     177 354     175 328
+//   1.6e8, 8 items        192  70    255  84    189  79     178 252     176 281
+//   5e8, 8 items          510  89    582 101    552 130     543 690     474 675
+//   1.3e9, 16 items      1270 148   1347 154   1243 192    1230 1525   1210 1370
+// (soups: random triangles of the size of the cloud, or a tenth of it.)
 constexpr double kMinPairs = 1.5e8;
 constexpr int64_t kMinPoints = 1024, kMinFaces = 2048;
 constexpr size_t kMaxTreeBytes = size_t{4} << 30;
 constexpr uint32_t kQueue = 192;    // leaves queued at most
 constexpr uint32_t kFull = kQueue - kWave;
+// Waves per leaf of points: one, or four where the points fill only about half of
+// the chip's wave slots.  Measured (us, all pairs, one wave, four): 1 x 8000
+// points against 20000 faces (small triangles) 208 128 84, large triangles 198 837
+// 379; 8 x 2777 against 7200 (height fields) 255 119 83; 1 x 22222 188 86 78; but 1 x
+// 31250 against 5120 (icospheres) 189 57 77.
+constexpr int64_t kFewPoints = 28000;
+constexpr int kSplitWaves = 4;
 constexpr int kThreads = 256;
 
 // A face's centroid, to sort by (vertex 0 for a face with a vertex index out
@@ -170,11 +185,17 @@ __device__ __forceinline__ bool reaches(const float4 &qlo, const float4 &qhi, co
     return lo.x <= hi.x && !(__builtin_fmaf(t, t * (1.0f - 0x1p-20f), -1e-37f) > worst);
 }
 
-__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(3, 8)))
+// A leaf of points per workgroup; each of its kWaves waves takes a share of the
+// leaves of faces.
+template <int kWaves>
+__global__ __launch_bounds__(kWaves * kWave) __attribute__((amdgpu_waves_per_eu(3, 8)))
 void face_search_kernel(SearchArgs a)
 {
-    __shared__ uint32_t queue[kQueue];
-    const uint32_t lane = threadIdx.x, sub = lane & 15u, row = lane >> 4;
+    __shared__ uint32_t queues[kWaves][kQueue];
+    __shared__ double part[kWaves][kLeaf];
+    const uint32_t lane = threadIdx.x % kWave, sub = lane & 15u, row = lane >> 4;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    uint32_t *queue = queues[wave];
     const uint32_t n = xcd_block();
     const uint32_t tiles = a.p.nodes * kNodeLeaves;
     const int64_t b = n / tiles;
@@ -189,7 +210,7 @@ void face_search_kernel(SearchArgs a)
     const float4 nlo = t.node[2 * n0], nhi = t.node[2 * n0 + 1];
     const float4 q = a.points[static_cast<int64_t>(n) * kLeaf + sub];
     const uint32_t np = static_cast<uint32_t>(a.p.n), nf = static_cast<uint32_t>(a.f.n);
-    if (nan_query(q, qhi) && row == 0u && __float_as_uint(q.z) < np) {   // no face is near it
+    if (nan_query(q, qhi) && threadIdx.x < kLeaf && __float_as_uint(q.z) < np) {   // no face is near it
         a.dist[b * np + __float_as_uint(q.z)] = __builtin_inff();
         a.fidx[b * np + __float_as_uint(q.z)] = -1;
     }
@@ -255,7 +276,7 @@ void face_search_kernel(SearchArgs a)
     for (bool first = true;; first = false) {
         drain(0u, 0u);
         if (!first) break;
-        gather(t, nlo, nhi, lane, done, queue, queued, kFull,
+        gather(t, nlo, nhi, lane, done, queue, queued, kFull, lane % kWaves == wave,
                [&](const float4 &lo, const float4 &hi) { return reaches(qlo, qhi, lo, hi, worst); }, drain);
     }
     double out = 0.0;
@@ -269,6 +290,13 @@ void face_search_kernel(SearchArgs a)
         out = sub == static_cast<uint32_t>(i) ? k : out;
     }
     out = rows_min(out);
+    if (kWaves > 1) {
+        if (row == 0u) part[wave][sub] = out;
+        __syncthreads();
+        if (wave > 0u) return;
+#pragma unroll
+        for (int w = 1; w < kWaves; ++w) out = min_key(out, part[w][sub]);
+    }
     if (id < np && row == 0u) {
         const int64_t o = b * np + id;
         const uint32_t face = static_cast<uint32_t>(__double2loint(out));
@@ -335,7 +363,11 @@ hipError_t launch_p2s_tree(int64_t B, int64_t S, int64_t nv, int64_t nf, const f
     a.fidx = fidx;
     a.p = pj.s;
     a.f = fj.s;
-    face_search_kernel<<<static_cast<uint32_t>(B * pj.s.nodes * kNodeLeaves), kWave, 0, stream>>>(a);
+    const uint32_t leaves = static_cast<uint32_t>(B * pj.s.nodes * kNodeLeaves);
+    if (B * S < kFewPoints)
+        face_search_kernel<kSplitWaves><<<leaves, kSplitWaves * kWave, 0, stream>>>(a);
+    else
+        face_search_kernel<1><<<leaves, kWave, 0, stream>>>(a);
     return hipGetLastError();
 }
 

@@ -321,12 +321,12 @@ __device__ __forceinline__ void append(uint32_t *list, uint32_t &n, bool take, u
 // (and of their node's) lets pass.  full(walked, ahead) is called when more than
 // `limit` are queued, with the nodes walked and those to walk still, and ends
 // the walk by returning false; it may empty the queue and tighten what takes()
-// lets pass.
+// lets pass.  mine: whether the wave takes this lane's leaf of each node.
 template <class Takes, class Full>
 __device__ __forceinline__ void gather(const Targets &j, const float4 &nlo, const float4 &nhi,
                                        uint32_t lane, const uint32_t done[4], uint32_t *queue,
-                                       uint32_t &queued, uint32_t limit, const Takes &takes,
-                                       const Full &full)
+                                       uint32_t &queued, uint32_t limit, bool mine,
+                                       const Takes &takes, const Full &full)
 {
     uint32_t walked = 0u;
     for (uint32_t from = 0; from < j.nodes; from += kWave) {
@@ -349,7 +349,7 @@ __device__ __forceinline__ void gather(const Targets &j, const float4 &nlo, cons
             ++walked;
             const uint32_t at = leaf_of(node), ahead = left != 0ull ? __builtin_ctzll(left) : node;
             const float4 alo = j.leaf[leaf_of(ahead) * 2], ahi = j.leaf[leaf_of(ahead) * 2 + 1];
-            bool take = takes(llo, lhi);
+            bool take = mine && takes(llo, lhi);
 #pragma unroll
             for (int v = 0; v < 4; ++v) take = take && done[v] != at;
             append(queue, queued, take, at);

@@ -54,9 +54,8 @@ def test_icospheres_match_all_pairs():
     _compare(*synth.p2s_workload(B=8, S=5001, level=4, seed=3), "icosphere")
 
 
-def _strain(name):
+def _strain(name, nf=3001, S=60007):
     rng = np.random.default_rng(5)
-    nf, S = 3001, 60007
     c = rng.uniform(-1, 1, (1, nf, 1, 3))
     tri = c + 0.03 * rng.normal(size=(1, nf, 3, 3))
     P = rng.uniform(-1.2, 1.2, (1, S, 3))
@@ -108,3 +107,19 @@ def test_strained_meshes_match_all_pairs(name):
     got = _compare(*_strain(name), name)
     if name == "all_invalid":
         assert bool(torch.isinf(got[0]).all()) and bool((got[1] == -1).all())
+
+
+# Few points: four waves share the faces of a leaf of points.
+@pytest.mark.parametrize("name", ["plain", "needles", "flat", "equal_faces", "equal_points",
+                                  "outliers", "invalid", "all_invalid", "nan_points",
+                                  "nan_vertices", "overflow"])
+def test_few_points_match_all_pairs(name):
+    _compare(*_strain(name, 13001, 13007), name)
+
+
+@pytest.mark.parametrize("B,S,n", [(1, 27999, 54), (1, 1024, 272), (20, 1100, 84)])
+def test_few_points_sizes_match_all_pairs(B, S, n):
+    V, F = synth.grid_mesh(B, n, n)
+    rng = np.random.default_rng(S)
+    P = np.concatenate([rng.uniform(-1.1, 1.1, (B, S, 2)), rng.normal(0, 0.2, (B, S, 1))], axis=2)
+    _compare(P.astype(np.float32), V, F, "grid")
