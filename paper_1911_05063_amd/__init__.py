@@ -174,19 +174,31 @@ def _distances(dist_xy: torch.Tensor, dist_yx: torch.Tensor) -> Tuple[torch.Tens
     return dxy, dyx
 
 
+def _scratch(device: torch.device, best, needed, *shape: int) -> torch.Tensor:
+    """Workspace for `shape` of best(*shape) bytes, or, where they cannot be
+    allocated, of the needed(*shape) bytes that the call takes too."""
+    n = best(*shape)
+    try:
+        return torch.empty(max(n, 1), dtype=torch.uint8, device=device)
+    except torch.OutOfMemoryError:
+        need = needed(*shape)
+        if need >= n:
+            raise
+        return torch.empty(max(need, 1), dtype=torch.uint8, device=device)
+
+
 def _forward_workspace(ws: Optional[torch.Tensor], B: int, N: int, M: int,
                        device: torch.device) -> torch.Tensor:
     """The caller's workspace if it is a large enough uint8 tensor on `device`,
-    else a new one (of the size with which cd_forward is fastest)."""
+    else a new one (of the size with which cd_forward is fastest, if it is free)."""
     lib = library()
     if ws is not None:
         ws = _device_tensor(ws, "workspace", torch.uint8)
         if ws.device != device:
             raise ValueError(f"workspace must be on {device} (got {ws.device})")
-        if ws.numel() >= int(lib.cd_workspace_bytes(B, N, M)):
+        if ws.numel() >= lib.cd_workspace_bytes(B, N, M):
             return ws
-    need = int(lib.cd_workspace_bytes_best(B, N, M))
-    return torch.empty(max(need, 1), dtype=torch.uint8, device=device)
+    return _scratch(device, lib.cd_workspace_bytes_best, lib.cd_workspace_bytes, B, N, M)
 
 
 # A small call is bound by its host side, and each launch passes these three (us,
@@ -511,8 +523,8 @@ def p2s_forward(P, V, F):
     B, S, nv, nf = P.shape[0], P.shape[1], V.shape[1], F.shape[1]
     dist = torch.empty((B, S), dtype=torch.float32, device=P.device)
     fidx = torch.empty((B, S), dtype=torch.int32, device=P.device)
-    need = int(library().cd_p2s_workspace_bytes_best(B, S, nv, nf))
-    ws = torch.empty(max(need, 1), dtype=torch.uint8, device=P.device)
+    ws = _scratch(P.device, library().cd_p2s_workspace_bytes_best,
+                  library().cd_p2s_workspace_bytes, B, S, nv, nf)
     with _on(P.device):
         _check(library().cd_p2s_forward(B, S, nv, nf, _ptr(P), _ptr(V), _ptr(F), _ptr(dist),
                                         _ptr(fidx), _ptr(ws), ws.numel(),

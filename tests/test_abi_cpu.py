@@ -461,3 +461,35 @@ def test_best_p2s_workspace(lib):
         assert best >= need and best % 256 == 0 and (best == 0) == (need == 0)
         pruned = B * S * nf >= 1.5e8 and 2 ** 21 >= S >= 1024 and nf >= 2048
         assert (best > need) == pruned, (B, S, nv, nf)
+
+
+def test_workspace_falls_back_to_the_needed_size(monkeypatch):
+    # Where the larger workspace cannot be allocated, the call takes the smaller
+    # one; where that fails too, the error is the caller's.
+    import torch
+    import paper_1911_05063_amd as cd
+    sizes, limit = [], 0
+    empty = torch.empty
+
+    def fake(n, **kw):
+        sizes.append(n)
+        if n > limit:
+            raise torch.OutOfMemoryError("no memory")
+        return empty(n, **kw)
+
+    B, N, M = 4, 16384, 16384
+    need, best = cd.workspace_bytes(B, N, M), cd.workspace_bytes_best(B, N, M)
+    assert best > need
+    monkeypatch.setattr(torch, "empty", fake)
+    cpu = torch.device("cpu")
+    for limit, want in ((best, [best]), (need, [best, need])):
+        sizes.clear()
+        assert cd._forward_workspace(None, B, N, M, cpu).numel() == want[-1]
+        assert sizes == want
+    limit = need - 1
+    with pytest.raises(torch.OutOfMemoryError):
+        cd._forward_workspace(None, B, N, M, cpu)
+    sizes.clear()
+    with pytest.raises(torch.OutOfMemoryError):     # nothing smaller to fall back to
+        cd._scratch(cpu, lambda: need, lambda: need)
+    assert sizes == [need]
