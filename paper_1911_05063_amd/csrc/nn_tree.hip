@@ -39,9 +39,9 @@
 //
 // Bound by instruction issue and latency (about 1600 VALU instructions per 16
 // queries on the mesh workload against 15000 for all pairs).  cd_forward, all
-// pairs -> this (us, calls back to back): 16 x 16384^2 mesh samples 525 -> 129; 4 x
-// 100000 x 10000 mixture 500 -> 175; 8 x 65536^2 grid points 3660 -> 201; 1 x 30000 x
-// 25001 110 -> 60; 1 x 200000^2 uniform 4600 -> 185.
+// pairs -> this (us, calls back to back): 16 x 16384^2 mesh samples 525 -> 126; 4 x
+// 100000 x 10000 mixture 505 -> 174; 8 x 65536^2 grid points 3660 -> 200; 1 x 30000 x
+// 25001 110 -> 57; 1 x 200000^2 uniform 4600 -> 184.
 #include "cd_internal.h"
 #include "fixed_point.h"
 #include "spatial_sort.h"
@@ -80,30 +80,19 @@ constexpr uint32_t kQueue = 192;    // leaves queued at most
 constexpr uint32_t kDrain = 32;     // leaves a single query queues before it visits them
 constexpr uint32_t kSplit = 128;    // and above this the queries are split
 static_assert(kSplit + kWave <= kQueue && kDrain + kWave <= kQueue, "a node's leaves fit the queue");
-// Where the heavy leaves' queries are expected to visit more than this share of
-// all leaves of targets, counting every leaf of the nodes within the bounds of
-// the leaf's box, all targets are taken instead (search_all).  Measured shares (us
-// with the tree, with all targets, and of the all-pairs search, which shares
-// its distances between the directions): template 4 x 60000 x 3001 0.19 (160, -, 115),
-// lognormal radii 64 x 4000^2 0.47 (374, -, 153), a sphere of 30000 points around 25001
-// 0.57 (500, -, 104), 16 x 16384^2 0.65 (3190, 1295, 510), around a cluster 0.82 (3740,
-// 1278, 510).  Handing such calls back to the all-pairs kernels (650 us) costs
-// two launches that mostly do nothing: 5 us of every call.
-constexpr double kAllShare = 0.56;
+// Where more than this share of all leaves of queries is heavy, and clouds are
+// not so large that kSplit leaves of targets are few, all targets are taken
+// instead (search_all).  Measured, share: us with the tree, with all targets, and of
+// the all-pairs search, which shares its distances between the directions:
+// template 16 x 15811^2 0.22: 385, -, 505; lognormal radii 64 x 4000^2 0.58: 374, -, 153;
+// a sphere of 30000 points around 25001 0.81: 500, 330, 105, 16 x 16384^2 0.84: 3190,
+// 1290, 505; around a cluster 1.0: 3740, 1280, 510.  (Lognormal radii 16 x 16384^2,
+// 0.82, take 1320 for 700.)  Handing such calls back to the all-pairs kernels
+// (650 us) costs two launches that mostly do nothing, 5 us of every call; a
+// count of the nodes in the bounds of each heavy leaf, for large clouds too, 3 us.
+constexpr double kAllShare = 0.75;
+constexpr double kAllMostPairs = 1.7e9;  // of an item (1 x 200000^2 lognormal, 0.58: 1260, all pairs 4800)
 constexpr uint32_t kList = 48;      // leaves listed per query
-
-// Sum over the wave, in every lane.
-__device__ __forceinline__ float wave_sum(float v)
-{
-    v += dpp_f<0xB1>(v);
-    v += dpp_f<0x4E>(v);
-    v += dpp_f<0x141>(v);
-    v += dpp_f<0x140>(v);
-    const auto r16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    v = __uint_as_float(r16[0]) + __uint_as_float(r16[1]);
-    const auto r32 = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return __uint_as_float(r32[0]) + __uint_as_float(r32[1]);
-}
 
 // The two directions of a call: queries of cloud k against the other cloud.
 struct SearchArgs {
@@ -113,19 +102,16 @@ struct SearchArgs {
     uint32_t *list;         // heavy leaves of queries (below)
     uint32_t leaves, items; // leaves of queries, over items and directions; items
     const float *cloud[2];  // [B, n, 3]
-    float most_visits;      // in units; with more all targets are taken
+    uint32_t most_heavy;    // leaves; with more all targets are taken
     SortShape s[2];
 };
 
 // The list of heavy leaves: kStripes lists, leaf n in list n % kStripes, so that
 // the waves that add to them seldom meet at one counter (10 ns each time; 32768
-// heavy leaves with one counter: 380 us).  Their heads, kStride words apart, then
-// their entries.  A head: the length, and the visits that the list is expected
-// to take, each of a leaf of targets by a query, in units of kVisitUnit (so that
-// they fit a word).
+// heavy leaves with one counter: 380 us).  Their lengths, kStride words apart, then
+// their entries.
 constexpr uint32_t kStripes = kWave;
 constexpr uint32_t kStride = 32;
-constexpr uint32_t kVisits = 1, kVisitUnit = 64;
 
 __host__ __device__ __forceinline__ uint32_t stripe_room(uint32_t leaves)
 {
@@ -237,15 +223,9 @@ void leaf_search_kernel(SearchArgs a)
            [&](const float4 &lo, const float4 &hi) { return within(qlo, qhi, lo, hi, worst, last); },
            [&](uint32_t, uint32_t) { heavy = true; return false; });
     if (heavy) {
-        const uint64_t near = __ballot(lane < j.t.nodes && within(qlo, qhi, nlo, nhi, worst, last));
         if (lane == 0u) {
-            // The place in the list and the visits in one atomic.
             const uint32_t s = n % kStripes, room = stripe_room(a.leaves);
-            const uint32_t nodes = static_cast<uint32_t>(__popcll(near)) * j.t.nodes /
-                                   min(j.t.nodes, static_cast<uint32_t>(kWave));
-            const uint64_t units = nodes * (kLeaf * kNodeLeaves / kVisitUnit);
-            const uint32_t at = static_cast<uint32_t>(atomicAdd(
-                reinterpret_cast<unsigned long long *>(a.list + s * kStride), units << 32 | 1u));
+            const uint32_t at = atomicAdd(a.list + s * kStride, 1u);
             if (at < room) a.list[kStripes * kStride + s * room + at] = n;
         }
         return;
@@ -378,11 +358,6 @@ void query_search_kernel(SearchArgs a)
     const uint32_t lane = threadIdx.x % kWave, sub = lane & 15u, row = lane >> 4;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     uint32_t *queue = queues[wave];
-    if (wave_sum(static_cast<float>(a.list[lane * kStride + kVisits])) > a.most_visits) {
-        const uint32_t groups = a.items * ((a.s[0].n + kWave - 1) / kWave + (a.s[1].n + kWave - 1) / kWave);
-        for (uint32_t g = blockIdx.x; g < groups; g += gridDim.x) search_all(a, g, wave, lane, part);
-        return;
-    }
     // Lane l: the entries of lists 0 to l.
     const uint32_t room = stripe_room(a.leaves);
     uint32_t upto = min(a.list[lane * kStride], room);
@@ -391,7 +366,12 @@ void query_search_kernel(SearchArgs a)
         const uint32_t o = __shfl_up(upto, d, kWave);
         upto += lane >= static_cast<uint32_t>(d) ? o : 0u;
     }
-    const uint32_t items = __builtin_amdgcn_readlane(upto, kWave - 1) * kLeaf;
+    const uint32_t heavy = __builtin_amdgcn_readlane(upto, kWave - 1), items = heavy * kLeaf;
+    if (heavy > a.most_heavy) {
+        const uint32_t groups = a.items * ((a.s[0].n + kWave - 1) / kWave + (a.s[1].n + kWave - 1) / kWave);
+        for (uint32_t g = blockIdx.x; g < groups; g += gridDim.x) search_all(a, g, wave, lane, part);
+        return;
+    }
     for (uint32_t item = blockIdx.x * kQueryWaves + wave; item < items; item += gridDim.x * kQueryWaves) {
         const uint32_t s = __popcll(__ballot(upto <= item / kLeaf));
         const uint32_t at = item / kLeaf - (s > 0u ? __builtin_amdgcn_readlane(upto, s - 1u) : 0u);
@@ -502,10 +482,9 @@ hipError_t launch_tree(int64_t B, int64_t N, int64_t M, const FwdArgs &f, hipStr
         B * (static_cast<int64_t>(s.s[0].nodes) + s.s[1].nodes) * kNodeLeaves);
     s.leaves = leaves;
     leaf_search_kernel<<<leaves, kWave, 0, stream>>>(s);
-    s.most_visits = static_cast<float>(
-        kAllShare * static_cast<double>(B) *
-        (static_cast<double>(N) * s.s[1].nodes + static_cast<double>(M) * s.s[0].nodes) *
-        (kNodeLeaves / kVisitUnit));
+    s.most_heavy = static_cast<double>(N) * M <= kAllMostPairs
+                       ? static_cast<uint32_t>(kAllShare * static_cast<double>(B) * (N + M) / kLeaf)
+                       : leaves;
     s.items = static_cast<uint32_t>(B);
     s.cloud[0] = f.X;
     s.cloud[1] = f.Y;
