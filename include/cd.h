@@ -75,7 +75,9 @@ size_t cd_workspace_bytes(int64_t B, int64_t N, int64_t M);
  * Bytes of device workspace with which cd_forward takes its fastest path for
  * this shape: cd_workspace_bytes, or more (about 50 bytes per point) where
  * sorting the clouds and skipping far targets is faster than all pairs (from
- * about 7e8 pairs on).  The results are the same bits either way.  0 where
+ * about 7e8 pairs on).  The results are the same bits either way.  That path's
+ * time depends on the clouds: where every point is about as far from all points
+ * of the other cloud, cd_workspace_bytes is the faster choice.  0 where
  * cd_workspace_bytes is.
  */
 size_t cd_workspace_bytes_best(int64_t B, int64_t N, int64_t M);
@@ -112,7 +114,7 @@ cd_status cd_forward(int64_t B, int64_t N, int64_t M,
  * Shapes whose cd_workspace_bytes(B, N, M) exceeds the limit (about 8.4
  * million points in B (N + M)) return CD_ERR_WORKSPACE with the sizes in
  * cd_last_error(); use cd_forward for them.  Those whose
- * cd_workspace_bytes_best(B, N, M) exceeds it (about 1.3 million points) take
+ * cd_workspace_bytes_best(B, N, M) exceeds it (about 1.4 million points) take
  * cd_forward's path for the smaller workspace.  Every call on one GPU shares
  * that GPU's array: calls that overlap in time on one GPU (two streams, two
  * threads) race and give undefined distances and indices (the indices are
@@ -292,7 +294,8 @@ size_t cd_p2s_workspace_bytes(int64_t B, int64_t S, int64_t nv, int64_t nf);
 /* Bytes of device workspace with which cd_p2s_forward takes its fastest path:
  * cd_p2s_workspace_bytes, or more where sorting points and faces to skip far
  * faces is faster than all pairs (from about 1.5e8 pairs and 2048 faces on).  The
- * results are the same bits either way. */
+ * results are the same bits either way.  Large triangles all over each other, or
+ * points about as far from all faces, are faster with cd_p2s_workspace_bytes. */
 size_t cd_p2s_workspace_bytes_best(int64_t B, int64_t S, int64_t nv, int64_t nf);
 
 /*

@@ -65,10 +65,10 @@ namespace {
 //   16 x 11180^2 (2e9)   283 240    281  98    281  81    280  75    285  90
 //   16 x 15811^2 (4e9)   505 385    517 117    513 102    514  94    513 118
 // The line is where every other kind gains at least a fifth, most of them twice;
-// templates lose up to 14% below 1.2e9 pairs, and up to 40% of a small cloud against
-// a large one.  Clouds where every query is as far from all targets (a sphere
-// around its centre) lose at any size, up to 3 times (kAllShare).  With a cloud of few points there is nothing to
-// skip (17 x 100000: 47 us either way).
+// templates lose up to 14% below 1.2e9 pairs, and up to 40% where a small cloud is
+// set against a large one.  Clouds where every query is as far from all targets
+// (a sphere around its centre) lose at any size, up to 3 times (kAllShare).  With
+// a cloud of few points there is nothing to skip (17 x 100000: 47 us either way).
 constexpr double kMinPairs = 7e8;
 constexpr int64_t kMinCloud = 1800;
 constexpr size_t kMaxTreeBytes = size_t{4} << 30;

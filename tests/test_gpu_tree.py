@@ -137,6 +137,31 @@ def test_nan_points_have_no_neighbour_and_are_none(name, N, M):
         assert torch.equal(a, b), f"{name} {what}: {int((a != b).sum())} differ"
 
 
+# Points with an infinite coordinate (their own results are not defined) and with
+# far ones whose squared distances overflow: all others as without them.
+@pytest.mark.parametrize("N,M", [(30011, 28000), (4001, 180001)])
+@pytest.mark.parametrize("name", ["ends", "scattered", "overflow"])
+def test_infinite_points_do_not_disturb_others(name, N, M):
+    g = torch.Generator(device="cuda:0").manual_seed(N + 1)
+    X, Y = (2 * torch.rand((1, n, 3), generator=g, device="cuda:0") - 1 for n in (N, M))
+    for P in (X, Y):
+        n = P.shape[1]
+        k = torch.tensor([0, n - 1]) if name == "ends" else torch.arange(5, n, 41)
+        k = k.to(P.device)
+        far = 3e25 if name == "overflow" else float("inf")
+        P[0, k, k % 3] = torch.where(k % 2 == 0, far, -far)
+    need, best = cd.workspace_bytes(1, N, M), cd.workspace_bytes_best(1, N, M)
+    assert best > need
+    print(f"[tree] infinite {name} N={N} M={M}", flush=True)
+    got = _call(X, Y, best)
+    fx, fy = ((P[0].abs() < 1e25).all(dim=1) for P in (X, Y))
+    ref = _without(X, Y, fx, fy)
+    for what, a, b, mine in zip(("dist_xy", "idx_xy", "dist_yx", "idx_yx"), got, ref, (fx, fx, fy, fy)):
+        assert torch.equal(a[:, mine], b[:, mine]), f"{name} {what}"
+    for i, n in ((got[1], M), (got[3], N)):
+        assert bool(((i >= -1) & (i < n)).all())
+
+
 def test_entry_points_take_the_same_path_and_bits():
     # Through the binding (default workspace), the static workspace and a graph.
     X_np, Y_np = synth.generate("mesh", 2, 20000, 18001, 5)
