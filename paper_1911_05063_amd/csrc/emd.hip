@@ -431,6 +431,7 @@ LseSplit split_for(int64_t B, int64_t nq, int64_t nt)
     l.nQG = static_cast<int>(ceil_div(nq, l.q * kWave));
     const int waves = l.few ? kLseFew : kLseWaves;
     const auto per = [&](int64_t n) { return ceil_div(ceil_div(n, waves), kLseStep) * kLseStep; };
+    // (None with two or four queries per lane: those leave a workgroup per CU.)
     const int64_t blocks = std::min(kCUs / groups(l.q), ceil_div(nt, waves * kLseStep));
     l.nTB = 1;
     l.TB = static_cast<int>(nt);
@@ -466,17 +467,19 @@ EmdLayout layout(int64_t B, int64_t N, int64_t M)
     return L;
 }
 
-template <bool kSplit>
-void launch_lse(int q, bool few, uint32_t grid, const LseArgs &a, hipStream_t stream)
+// (Targets are split only with one query per lane and more than 64 targets.)
+void launch_lse(const LseSplit &l, uint32_t grid, const LseArgs &a, hipStream_t stream)
 {
-    const int waves = few ? kLseFew : kLseWaves;
+    const int waves = l.few ? kLseFew : kLseWaves;
     const auto run = [&](auto kernel) { kernel<<<grid, waves * kWave, 0, stream>>>(a); };
-    if (q == 4)
-        run(few ? lse_kernel<4, 8, kLseFew, kSplit> : lse_kernel<4, 8, kLseWaves, kSplit>);
-    else if (q == 2)
-        run(few ? lse_kernel<2, 16, kLseFew, kSplit> : lse_kernel<2, 16, kLseWaves, kSplit>);
+    if (l.nTB > 1)
+        run(lse_kernel<1, 16, kLseWaves, true>);
+    else if (l.q == 4)
+        run(l.few ? lse_kernel<4, 8, kLseFew, false> : lse_kernel<4, 8, kLseWaves, false>);
+    else if (l.q == 2)
+        run(l.few ? lse_kernel<2, 16, kLseFew, false> : lse_kernel<2, 16, kLseWaves, false>);
     else
-        run(few ? lse_kernel<1, 16, kLseFew, kSplit> : lse_kernel<1, 16, kLseWaves, kSplit>);
+        run(l.few ? lse_kernel<1, 16, kLseFew, false> : lse_kernel<1, 16, kLseWaves, false>);
 }
 
 // One half-update of the queries' potentials.
@@ -503,11 +506,7 @@ void lse_pass(int64_t B, const float *Q, float4 *Q4, int64_t nq, const float4 *T
     const int64_t tiles = B * l.nQG * l.nTB;
     for (int64_t first = 0; first < tiles; first += kLseGrid) {
         a.first = static_cast<uint32_t>(first);
-        const uint32_t grid = static_cast<uint32_t>(std::min(tiles - first, kLseGrid));
-        if (l.nTB > 1)
-            launch_lse<true>(l.q, l.few, grid, a, stream);
-        else
-            launch_lse<false>(l.q, l.few, grid, a, stream);
+        launch_lse(l, static_cast<uint32_t>(std::min(tiles - first, kLseGrid)), a, stream);
     }
     if (l.nTB > 1)
         lse_merge_kernel<<<static_cast<uint32_t>(ceil_div(B * nq, kWave)), kWave, 0, stream>>>(a, B);

@@ -63,14 +63,12 @@ def test_one_iteration_matches_oracle(B, N, M, eps):
     assert np.max(np.abs(g - G_or)) <= tol_g, (np.max(np.abs(g - G_or)), tol_g)
 
 
-def test_partials_merged_in_chunks_match_oracle():
-    # B*ceil(N/1024) = 512 query groups: the f-update takes Y as one block of
-    # 1100 targets, so from the second iteration on it merges the g-update's
-    # partials (Y against 2 blocks of X) for its block in two LDS chunks, the
-    # second one with a 12-target tail.  Items are independent: the oracle
-    # checks three of the 128.
+def test_many_large_groups_match_oracle():
+    # 2048 and 640 groups of 256 queries, 16 waves each: 80 targets a wave with a
+    # tail for X, 256 for Y (whose last group has 76 queries).  Items are
+    # independent: the oracle checks three of the 128.
     B, N, M, iters, e0, e1 = 128, 4096, 1100, 3, 0.3, 0.1
-    print(f"[case] emd chunked partials B={B} N={N} M={M}", flush=True)
+    print(f"[case] emd large groups B={B} N={N} M={M}", flush=True)
     X, Y = synth.generate("sphere", B, N, M, 13)
     cost, f, g = cd.emd_forward(gc.to_gpu(X), gc.to_gpu(Y), e0, e1, iters)
     f, g = gc.to_np(f), gc.to_np(g)
@@ -150,8 +148,9 @@ def test_reproducible():
 @pytest.mark.parametrize("B,N,M", [(256, 33, 65), (260, 257, 15), (130, 200, 255), (140, 129, 17),
                                    (1, 16, 1), (2, 63, 2049), (3, 65, 16)])
 def test_every_split_of_a_half_update_matches_oracle(B, N, M):
-    # 4, 2 and 1 queries per lane (as many as leave 256 workgroups), targets
-    # that leave waves empty, with one target, and with tails.
+    # 4, 2 and 1 queries per lane (as many as leave 256 workgroups and as the
+    # item has), 16 waves or 4, targets that leave waves empty, with one target,
+    # and with tails.
     eps = 0.05
     print(f"[case] emd split B={B} N={N} M={M}", flush=True)
     X, Y = synth.generate("gmm", B, N, M, 3 * N + M)
