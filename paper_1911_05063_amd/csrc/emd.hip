@@ -60,6 +60,7 @@ constexpr int kLseWaves = 16;               // waves of a half-update's workgrou
 // some of them run.  (A loop over groups in the kernel: 7.0 -> 8.0 us a
 // half-update of 2 x 500 x 701.)
 constexpr int64_t kLseGrid = 1 << 21;
+constexpr int64_t kPlanGrid = 1 << 23;      // the same for workgroups of 256 threads
 constexpr int kLseFew = 4;                  // waves where the targets are few
 constexpr int kLseStep = 16;                // targets per wave: a multiple
 constexpr int kSplitGain = 64;              // targets per wave that a split has to save
@@ -247,6 +248,7 @@ struct PlanArgs {
     float k;                // log2(e) / eps
     float mass;             // a b = 1 / (nq nt)
     int nQG, nTB, TB;
+    uint32_t first;         // tile of the launch's first workgroup
 };
 
 template <bool kGrad>
@@ -281,9 +283,9 @@ template <bool kGrad>
 __global__ __launch_bounds__(kEThreads) void plan_kernel(PlanArgs a)
 {
     __shared__ double red[kEThreads / kWave];
-    const int64_t per_item = static_cast<int64_t>(a.nQG) * a.nTB;
-    const int64_t b = blockIdx.x / per_item;
-    const int rest = static_cast<int>(blockIdx.x % per_item);
+    const int64_t per_item = static_cast<int64_t>(a.nQG) * a.nTB, tile = a.first + blockIdx.x;
+    const int64_t b = tile / per_item;
+    const int rest = static_cast<int>(tile % per_item);
     const int qg = rest / a.nTB, tb = rest % a.nTB;
     const int64_t q0 = static_cast<int64_t>(qg) * kEGroup;
     float qx[kEQ], qy[kEQ], qz[kEQ], qk[kEQ], acc[kEQ], gx[kEQ], gy[kEQ], gz[kEQ];
@@ -359,10 +361,10 @@ __global__ __launch_bounds__(kEThreads) void plan_kernel(PlanArgs a)
 }
 
 __global__ __launch_bounds__(kThreads) void cost_reduce_kernel(const double *part, int64_t tiles,
-                                                               float mass, float *cost)
+                                                               float mass, int64_t first, float *cost)
 {
     __shared__ double red[kThreads / kWave];
-    const int64_t b = blockIdx.x;
+    const int64_t b = first + blockIdx.x;
     double t = 0.0;
     for (int64_t i = threadIdx.x; i < tiles; i += kThreads) t += part[b * tiles + i];
 #pragma unroll
@@ -533,11 +535,15 @@ hipError_t plan_pass(int64_t B, const float *Q, int64_t nq, const float *T, int6
     a.nQG = t.nQG;
     a.nTB = t.nTB;
     a.TB = t.TB;
-    const uint32_t grid = static_cast<uint32_t>(B * t.nQG * t.nTB);
-    if (gradient)
-        plan_kernel<true><<<grid, kEThreads, 0, stream>>>(a);
-    else
-        plan_kernel<false><<<grid, kEThreads, 0, stream>>>(a);
+    const int64_t tiles = B * t.nQG * t.nTB;
+    for (int64_t first = 0; first < tiles; first += kPlanGrid) {
+        a.first = static_cast<uint32_t>(first);
+        const uint32_t grid = static_cast<uint32_t>(std::min(tiles - first, kPlanGrid));
+        if (gradient)
+            plan_kernel<true><<<grid, kEThreads, 0, stream>>>(a);
+        else
+            plan_kernel<false><<<grid, kEThreads, 0, stream>>>(a);
+    }
     if (gradient && t.nTB > 1)
         grad_merge_kernel<<<static_cast<uint32_t>(ceil_div(B * nq * 3, kThreads)), kThreads, 0,
                             stream>>>(a, B);
@@ -585,9 +591,10 @@ hipError_t launch_emd_forward(int64_t B, int64_t N, int64_t M, const float *X, c
     e = plan_pass(B, X, N, Y, M, f, g, eps, L.xy, false, nullptr, cost_part, nullptr,
                              nullptr, stream);
     if (e != hipSuccess) return e;
-    cost_reduce_kernel<<<static_cast<uint32_t>(B), kThreads, 0, stream>>>(
-        cost_part, static_cast<int64_t>(L.xy.nQG) * L.xy.nTB,
-        static_cast<float>(1.0 / (static_cast<double>(N) * static_cast<double>(M))), cost);
+    for (int64_t first = 0; first < B; first += kPlanGrid)
+        cost_reduce_kernel<<<static_cast<uint32_t>(std::min(B - first, kPlanGrid)), kThreads, 0, stream>>>(
+            cost_part, static_cast<int64_t>(L.xy.nQG) * L.xy.nTB,
+            static_cast<float>(1.0 / (static_cast<double>(N) * static_cast<double>(M))), first, cost);
     return hipGetLastError();
 }
 

@@ -222,3 +222,22 @@ def test_split_targets_match_oracle(B, N, M):
     tol = 4 * _step_tol(eps, 512, _cmax(X[items], Y[items]), pmax)
     assert np.max(np.abs(gc.to_np(f)[items] - F_or)) <= tol
     assert np.max(np.abs(gc.to_np(g)[items] - G_or)) <= tol
+
+
+def test_tens_of_millions_of_single_points():
+    # More than 2^24 workgroups of 256 threads in the plan passes.  With one
+    # point each the plan is 1, the cost the distance, the gradients its unit vectors.
+    B = 17_000_000
+    print(f"[case] emd single points B={B}", flush=True)
+    gen = torch.Generator(device="cuda:0").manual_seed(6)
+    X, Y = (torch.rand((B, 1, 3), generator=gen, device="cuda:0") + k for k in (0.0, 1.0))
+    cost, f, g = cd.emd_forward(X, Y, 0.1, 0.1, 1)
+    d = (X - Y)[:, 0].double()
+    want = d.norm(dim=1)
+    # f + g = C to a few roundings of it, which the plan's exponent takes over eps.
+    assert float((cost / want - 1.0).abs().max()) <= 2.0 ** -17
+    go = torch.ones(B, device="cuda:0")
+    gX, gY = cd.emd_backward(X, Y, f, g, 0.1, go)
+    unit = d / want[:, None]
+    for got, ref in ((gX, unit), (gY, -unit)):
+        assert float((got[:, 0] - ref).abs().max()) <= 2.0 ** -17
