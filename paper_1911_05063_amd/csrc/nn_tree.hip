@@ -221,7 +221,7 @@ void leaf_search_kernel(SearchArgs a)
     bool heavy = false;
     gather(j.t, nlo, nhi, lane, done, queue, queued, kSplit, true,
            [&](const float4 &lo, const float4 &hi) { return within(qlo, qhi, lo, hi, worst, last); },
-           [&](uint32_t, uint32_t) { heavy = true; return false; });
+           [&] { heavy = true; return false; });
     if (heavy) {
         if (lane == 0u) {
             const uint32_t s = n % kStripes, room = stripe_room(a.leaves);
@@ -405,7 +405,7 @@ void query_search_kernel(SearchArgs a)
             settle();
         }
         uint32_t queued = 0u;
-        const auto drain = [&](uint32_t, uint32_t) {
+        const auto drain = [&] {
             wave_sync();
             for (uint32_t c = 0u; c < queued; c += 16u) {
                 float4 t[4];
@@ -423,7 +423,7 @@ void query_search_kernel(SearchArgs a)
         gather(j.t, nlo, nhi, lane, done, queue, queued, kDrain, true,
                [&](const float4 &lo, const float4 &hi) { return within(q, q, lo, hi, worst, last); },
                drain);
-        drain(0u, 0u);
+        drain();
         if (lane == 0u) j.store(id, high(best), static_cast<uint32_t>(__double2loint(best)));
     }
 }

@@ -255,9 +255,11 @@ void face_search_kernel(SearchArgs a)
     };
     uint32_t done[4];
     nearest_leaves(t, qlo, qhi, nlo, nhi, lane, done);
-    if (lane < 4u) queue[lane] = done[0] == kNoPoint ? 0u : lane == 0u ? done[0] : lane == 1u ? done[1] : lane == 2u ? done[2] : done[3];
+    if (lane < 4u)
+        queue[lane] = done[0] == kNoPoint ? 0u : lane == 0u ? done[0] : lane == 1u ? done[1]
+                      : lane == 2u        ? done[2] : done[3];
     uint32_t queued = done[0] != kNoPoint ? 4u : 0u;
-    const auto drain = [&](uint32_t, uint32_t) __attribute__((always_inline)) {
+    const auto drain = [&]() __attribute__((always_inline)) {
         wave_sync();
         for (uint32_t c = 0u; c < queued; c += 4u) {
             const uint32_t leaf = queue[min(c + row, queued - 1u)];
@@ -274,7 +276,7 @@ void face_search_kernel(SearchArgs a)
         return true;
     };
     for (bool first = true;; first = false) {
-        drain(0u, 0u);
+        drain();
         if (!first) break;
         gather(t, nlo, nhi, lane, done, queue, queued, kFull, lane % kWaves == wave,
                [&](const float4 &lo, const float4 &hi) { return reaches(qlo, qhi, lo, hi, worst); }, drain);

@@ -318,17 +318,16 @@ __device__ __forceinline__ void append(uint32_t *list, uint32_t &n, bool take, u
 }
 
 // Queues the leaves, other than the four done, that takes(lo, hi) of their box
-// (and of their node's) lets pass.  full(walked, ahead) is called when more than
-// `limit` are queued, with the nodes walked and those to walk still, and ends
-// the walk by returning false; it may empty the queue and tighten what takes()
-// lets pass.  mine: whether the wave takes this lane's leaf of each node.
+// (and of their node's) lets pass.  full() is called when more than `limit` are
+// queued and ends the walk by returning false; it may empty the queue and
+// tighten what takes() lets pass.  mine: whether the wave takes this lane's leaf
+// of each node.
 template <class Takes, class Full>
 __device__ __forceinline__ void gather(const Targets &j, const float4 &nlo, const float4 &nhi,
                                        uint32_t lane, const uint32_t done[4], uint32_t *queue,
                                        uint32_t &queued, uint32_t limit, bool mine,
                                        const Takes &takes, const Full &full)
 {
-    uint32_t walked = 0u;
     for (uint32_t from = 0; from < j.nodes; from += kWave) {
         float4 lo = nlo, hi = nhi;
         if (from > 0u) {
@@ -346,7 +345,6 @@ __device__ __forceinline__ void gather(const Targets &j, const float4 &nlo, cons
         float4 llo = j.leaf[leaf_of(node) * 2], lhi = j.leaf[leaf_of(node) * 2 + 1];
         while (left != 0ull) {
             left &= left - 1ull;
-            ++walked;
             const uint32_t at = leaf_of(node), ahead = left != 0ull ? __builtin_ctzll(left) : node;
             const float4 alo = j.leaf[leaf_of(ahead) * 2], ahi = j.leaf[leaf_of(ahead) * 2 + 1];
             bool take = mine && takes(llo, lhi);
@@ -357,8 +355,7 @@ __device__ __forceinline__ void gather(const Targets &j, const float4 &nlo, cons
             llo = alo;
             lhi = ahi;
             if (queued <= limit) continue;
-            if (!full(walked, static_cast<uint32_t>(__popcll(left)) + (j.nodes - min(from + kWave, j.nodes))))
-                return;
+            if (!full()) return;
             left &= __ballot(takes(lo, hi));
             if (left != 0ull && static_cast<uint32_t>(__builtin_ctzll(left)) != node) {
                 node = __builtin_ctzll(left);
